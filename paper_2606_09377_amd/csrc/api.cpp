@@ -25,6 +25,7 @@
 #include <cstdio>
 #include <cstring>
 #include <deque>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -51,11 +52,8 @@ vcr_status graph_plan(vcr_ctx *c, int32_t B, int32_t m, int *chunk_out, size_t *
 namespace {
 
 void free_layers(vcr_ctx *c) {
-  for (auto &L : c->layers) {
-    if (L.Wp) (void)hipFree(L.Wp);
-    if (L.Bt) (void)hipFree(L.Bt);
-    if (L.b) (void)hipFree(L.b);
-  }
+  if (c->layer_base) (void)hipFree(c->layer_base);
+  c->layer_base = nullptr;
   c->layers.clear();
 }
 
@@ -131,6 +129,11 @@ vcr_status ensure_ws(vcr_ctx *c, size_t bytes) {
   free_ws(c);
   void *p = nullptr;
   hipError_t e = hipMalloc(&p, bytes);
+  if (e != hipSuccess && c->split_base) {   // the split weights make room
+    (void)hipGetLastError();
+    drop_split_operands(c);
+    e = hipMalloc(&p, bytes);
+  }
   if (e != hipSuccess) {
     (void)hipGetLastError();
     return fail(c, VCR_ERR_OOM, "hipMalloc(%llu) failed: %s", (unsigned long long)bytes, hipGetErrorString(e));
@@ -142,6 +145,46 @@ vcr_status ensure_ws(vcr_ctx *c, size_t bytes) {
   // the A buffers' padding rows/columns are read by the GEMM: start from zeros
   HIP_TRY(c, launch_fill(reinterpret_cast<float *>(p), (int64_t)(bytes / 4), 0.f, c->stream));
   return VCR_OK;
+}
+
+vcr_status split_operands(vcr_ctx *c, const std::vector<SplitItem> &items) {
+  size_t bytes = 0, free_b = 0, total_b = 0;
+  for (const SplitItem &it : items) bytes += al(sizeof(uint16_t) * 3 * (size_t)it.N * (size_t)it.K);
+  if (bytes == 0) return VCR_OK;
+  HIP_TRY(c, hipMemGetInfo(&free_b, &total_b));
+  if (bytes + total_b / 8 > free_b) return VCR_OK;
+  void *base = nullptr;
+  if (hipMalloc(&base, bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    return VCR_OK;
+  }
+  c->split_base = base;
+  c->split_bytes = bytes;
+  size_t off = 0;
+  for (const SplitItem &it : items) {
+    *it.dst = reinterpret_cast<uint16_t *>(static_cast<char *>(base) + off);
+    c->split_ptrs.push_back(it.dst);
+    const hipError_t e = launch_split_weights(it.src, it.ld, it.N, it.K, *it.dst, c->stream);
+    if (e != hipSuccess) {
+      drop_split_operands(c);
+      return fail(c, VCR_ERR_DEVICE, "launch_split_weights: %s", hipGetErrorString(e));
+    }
+    off += al(sizeof(uint16_t) * 3 * (size_t)it.N * (size_t)it.K);
+  }
+  c->net_bytes += bytes;
+  return VCR_OK;
+}
+
+void drop_split_operands(vcr_ctx *c) {
+  for (uint16_t **p : c->split_ptrs) *p = nullptr;
+  c->split_ptrs.clear();
+  if (!c->split_base) return;
+  (void)hipDeviceSynchronize();   // launches on any stream may still read them
+  (void)hipFree(c->split_base);
+  c->split_base = nullptr;
+  c->net_bytes -= std::min(c->net_bytes, c->split_bytes);
+  c->split_bytes = 0;
+  ++c->net_epoch;   // a recorded graph holds their addresses
 }
 
 namespace {
@@ -301,6 +344,7 @@ void vcr_destroy(vcr_ctx *c) {
   if (c->device >= 0) {
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
+    drop_split_operands(c);
     free_layers(c);
     free_ws(c);
     if (c->d_counters) (void)hipFree(c->d_counters);
@@ -388,6 +432,7 @@ vcr_status vcr_load_net(vcr_ctx *c, const vcr_node *nodes, int32_t n, const int3
     if (c->device >= 0) {
       HIP_TRY(c, hipSetDevice(c->device));
       HIP_TRY(c, hipStreamSynchronize(c->stream));
+      drop_split_operands(c);
       free_layers(c);
       free_ws(c);
     }
@@ -399,6 +444,10 @@ vcr_status vcr_load_net(vcr_ctx *c, const vcr_node *nodes, int32_t n, const int3
     return VCR_OK;
   }
   if (st != VCR_OK) return st;
+  if (c->device >= 0) {
+    HIP_TRY(c, hipSetDevice(c->device));
+    drop_split_operands(c);
+  }
   destroy_graph(c->graph);
   c->graph = nullptr;
   if (c->device < 0) {
@@ -430,8 +479,9 @@ vcr_status vcr_load_net(vcr_ctx *c, const vcr_node *nodes, int32_t n, const int3
   c->loaded = false;
   c->relu_n.clear();
   c->n0 = in_chw[0];
+  // one allocation for every layer's arrays and one staging buffer of the largest layer
   int64_t prev = in_chw[0];
-  float *staging = nullptr;
+  size_t bytes = 0, staging_bytes = 0;
   for (int32_t i = 0; i < n; ++i) {
     if (nodes[i].op == VCR_RELU) {
       c->relu_n.push_back((int32_t)prev);
@@ -442,28 +492,51 @@ vcr_status vcr_load_net(vcr_ctx *c, const vcr_node *nodes, int32_t n, const int3
     L.n_out = nodes[i].out_features;
     L.ld_in = ld_of(L.n_in);
     L.ld_out = ld_of(L.n_out);
-    const size_t wbytes = sizeof(float) * (size_t)L.n_out * L.n_in;
-    HIP_TRY(c, hipMalloc(&staging, wbytes));
-    HIP_TRY(c, hipMemcpy(staging, nodes[i].W, wbytes, hipMemcpyHostToDevice));
-    HIP_TRY(c, hipMalloc(&L.Wp, sizeof(float) * (size_t)L.ld_out * L.ld_in));
-    HIP_TRY(c, hipMalloc(&L.Bt, sizeof(float) * (size_t)L.ld_in * L.ld_out));
-    HIP_TRY(c, hipMalloc(&L.b, sizeof(float) * (size_t)L.ld_out));
     c->layers.push_back(L);
+    bytes += 2 * al(sizeof(float) * (size_t)L.ld_out * L.ld_in) + al(sizeof(float) * (size_t)L.ld_out);
+    staging_bytes = std::max(staging_bytes, sizeof(float) * (size_t)L.n_out * L.n_in);
+    prev = L.n_out;
+  }
+  HIP_TRY(c, hipMalloc(&c->layer_base, bytes));
+  float *staging = nullptr;
+  HIP_TRY(c, hipMalloc(&staging, staging_bytes));
+  struct Free {
+    float *p;
+    ~Free() { (void)hipFree(p); }
+  };
+  std::unique_ptr<Free> staging_owner(new Free{staging});
+  Workspace w;
+  w.base = static_cast<char *>(c->layer_base);
+  w.cap = bytes;
+  size_t k = 0;
+  for (int32_t i = 0; i < n; ++i) {
+    if (nodes[i].op == VCR_RELU) continue;
+    DenseLayer &L = c->layers[k++];
+    L.Wp = take<float>(w, (size_t)L.ld_out * L.ld_in);
+    L.Bt = take<float>(w, (size_t)L.ld_in * L.ld_out);
+    L.b = take<float>(w, (size_t)L.ld_out);
+    HIP_TRY(c, hipMemcpyAsync(staging, nodes[i].W, sizeof(float) * (size_t)L.n_out * L.n_in, hipMemcpyHostToDevice,
+                              c->stream));
     // Wp: row-major copy, zero-padded to [ld_out][ld_in] (a transpose of the transpose); the
     // alpha-CROWN gradient pass uses it as a GEMM operand
     HIP_TRY(c, launch_transpose_pad(staging, L.n_out, L.n_in, L.Bt, L.ld_out, L.ld_in, c->stream));
     HIP_TRY(c, launch_transpose_pad(L.Bt, (int32_t)L.ld_in, (int32_t)L.ld_out, L.Wp, L.ld_in, L.ld_out, c->stream));
     HIP_TRY(c, launch_fill(L.b, L.ld_out, 0.f, c->stream));
-    HIP_TRY(c, hipStreamSynchronize(c->stream));
-    HIP_TRY(c, hipMemcpy(L.b, nodes[i].b, sizeof(float) * L.n_out, hipMemcpyHostToDevice));
-    HIP_TRY(c, hipFree(staging));
-    staging = nullptr;
-    prev = L.n_out;
+    HIP_TRY(c, hipMemcpyAsync(L.b, nodes[i].b, sizeof(float) * L.n_out, hipMemcpyHostToDevice, c->stream));
   }
-  HIP_TRY(c, hipDeviceSynchronize());
+  staging_owner.reset();   // waits for the copies
   c->net_bytes = 0;
   for (const DenseLayer &L : c->layers)
     c->net_bytes += sizeof(float) * (2 * (uint64_t)L.ld_in * L.ld_out + (uint64_t)L.ld_out);
+  std::vector<SplitItem> items;
+  for (size_t j = 0; j + 1 < c->layers.size(); ++j) {   // the last layer is no product's operand
+    DenseLayer &L = c->layers[j];
+    items.push_back({L.Bt, L.ld_out, L.ld_in, L.ld_out, &L.Bs});
+    items.push_back({L.Wp, L.ld_in, L.ld_out, L.ld_in, &L.Ws});
+  }
+  st = split_operands(c, items);
+  if (st != VCR_OK) return st;
+  HIP_TRY(c, hipDeviceSynchronize());
   c->loaded = true;
   return VCR_OK;
 }
@@ -545,7 +618,10 @@ vcr_status ibp_layer(vcr_ctx *c, const DenseLayer &W, const float *cin, const fl
   GemmArgs g{};
   g.lda = W.ld_in;
   g.Bt = W.Wp;
+  g.Bs = W.Ws;
   g.ldb = W.ld_in;
+  g.N = W.n_out;
+  g.K_real = W.n_in;
   g.M = B;
   g.M_pad = (int32_t)M_pad;
   g.K = (int32_t)W.ld_in;
@@ -672,7 +748,10 @@ vcr_status run_chain(vcr_ctx *c, CallBufs &bf, int top, int32_t M, int32_t rows_
     g.A = bf.A[cur];
     g.lda = W.ld_out;
     g.Bt = W.Bt;
+    g.Bs = W.Bs;
     g.ldb = W.ld_out;
+    g.N = W.n_in;
+    g.K_real = W.n_out;
     g.M = M;
     g.M_pad = M_pad;
     g.K = (int32_t)W.ld_out;
@@ -815,7 +894,10 @@ vcr_status alpha_spec(vcr_ctx *c, CallBufs &bf, const Plan &p, const AlphaCall &
         g.A = bf.A[(k - 1) & 1];
         g.lda = W.ld_in;
         g.Bt = W.Wp;
+        g.Bs = W.Ws;
         g.ldb = W.ld_in;
+        g.N = W.n_out;
+        g.K_real = W.n_in;
         g.M = M;
         g.M_pad = M_pad;
         g.K = (int32_t)W.ld_in;

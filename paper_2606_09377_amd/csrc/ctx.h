@@ -27,6 +27,10 @@ struct DenseLayer {
   float *Wp = nullptr;   // n_out x ld_in, zero padded
   float *Bt = nullptr;   // ld_in x ld_out, Bt[n][k] = W[k][n], zero padded
   float *b = nullptr;    // ld_out, zero padded
+  // split copies (split_bf16.h) of Bt and Wp, the operands of the backward and of the forward
+  // and IBP products; null on the last layer (never a product's operand) and where the device
+  // has no room for them (split_operands)
+  uint16_t *Bs = nullptr, *Ws = nullptr;
 };
 
 struct Workspace {
@@ -55,11 +59,17 @@ struct vcr_ctx {
   bool loaded = false;
   int32_t n0 = 0;
   std::vector<DenseLayer> layers;   // the MLP chain
+  void *layer_base = nullptr;       // the allocation that holds its arrays
   std::vector<int32_t> relu_n;      // neurons per ReLU node
   int32_t n_out = 0;                // outputs of the loaded network (the last dense node)
   // workspace
   Workspace ws;
   uint64_t peak_ws = 0;
+  // split weight operands: one allocation, and the layers' pointers into it (set to null when
+  // it is given back)
+  void *split_base = nullptr;
+  uint64_t split_bytes = 0;
+  std::vector<uint16_t **> split_ptrs;
   uint64_t net_bytes = 0;   // device memory holding the loaded network (weights in their layouts)
   // last call
   int32_t last_B = 0;
@@ -166,6 +176,20 @@ T *take(vcr_ctx *c, size_t count) {
 }
 
 vcr_status ensure_ws(vcr_ctx *c, size_t bytes);
+
+// A weight operand [N][K] (float32, pitch ld) to be split into *dst.
+struct SplitItem {
+  const float *src;
+  int64_t ld, N, K;
+  uint16_t **dst;
+};
+// Splits the operands of a network being loaded.  The copies cost 6 bytes a weight beside the
+// float32 weights, which stay: where less than an eighth of the device's memory would remain
+// free beside them, or a later workspace needs the room (ensure_ws), there are none and the
+// products run on the float32 matrix instructions, so that what a device can load and bound
+// does not shrink.
+vcr_status split_operands(vcr_ctx *c, const std::vector<SplitItem> &items);
+void drop_split_operands(vcr_ctx *c);
 
 namespace vcr {
 // Resolves the device address of the allocation-free scratch on c's device (current) into

@@ -50,17 +50,18 @@ constexpr int GEMM_MINB = BK == 32 ? 2 : 3;   // workgroups per CU the registers
 constexpr int NTHREADS = 256;
 constexpr int GROUP_M = 8;
 
-__device__ __forceinline__ void map_tile(int bid, int G, int n_mt, int n_nt, int &mt, int &nt) {
+__device__ __forceinline__ void map_tile(int bid, int G, int n_mt, int n_nt, int &mt, int &nt,
+                                         int group_m = GROUP_M) {
   // Workgroup ids are spread over the 8 XCDs round robin; hand each XCD a contiguous range
   // of logical tiles so the tiles sharing operands also share that XCD's L2.
   const int x = bid & 7, t = bid >> 3;
   const int q = G >> 3, rem = G & 7;
   const int logical = x * q + min(x, rem) + t;
-  // Grouped order: GROUP_M row blocks sweep every column tile together.
-  const int per_group = GROUP_M * n_nt;
+  // Grouped order: group_m row blocks sweep every column tile together.
+  const int per_group = group_m * n_nt;
   const int g = logical / per_group;
-  const int first_m = g * GROUP_M;
-  const int gm = min(GROUP_M, n_mt - first_m);
+  const int first_m = g * group_m;
+  const int gm = min(group_m, n_mt - first_m);
   const int idx = logical - g * per_group;
   mt = first_m + idx % gm;
   nt = idx / gm;
@@ -592,8 +593,15 @@ __global__ __launch_bounds__(256) void k_gemm_mid(const GemmArgs p) {
                                     reinterpret_cast<signed char *>(&As[0][0]));
 }
 
+}  // namespace vcr
+
+#include "gemm_split.h"
+
+namespace vcr {
+
 int gemm_kind(const GemmArgs &a) {
   if (a.M_pad <= 0 || a.N_pad <= 0) return 0;
+  if (a.Bs) return split_kind(a);
   const int64_t grid = (int64_t)(a.M_pad / BM) * (a.N_pad / BN);
   const int64_t mid = (int64_t)(a.M_pad / MD_BM) * (a.N_pad / MD_BN);
   const int64_t last = grid % GEMM_ROUND;
@@ -618,6 +626,15 @@ hipError_t launch_gemm(const GemmArgs &a, hipStream_t s) {
   const bool al = a.alpha || a.pre;
   if (a.mode != EPI_RELAX && a.mode != EPI_CONCRETIZE && a.mode != EPI_FORWARD && a.mode != EPI_AFFINE)
     return hipErrorInvalidValue;
+  if (a.Bs) {
+    if (a.M <= 0 || a.M > a.M_pad || a.N <= 0 || a.N > a.N_pad || a.K_real <= 0 || a.K_real > a.K || a.lda % 4 || ld % 4)
+      return hipErrorInvalidValue;
+    switch (gemm_kind(a)) {
+      case 0: return launch_split_tile<SplitL>(a, s);
+      case 3: return launch_split_tile<SplitM>(a, s);
+      default: return launch_split_tile<SplitS>(a, s);
+    }
+  }
   const int64_t mid = (int64_t)(a.M_pad / MD_BM) * (a.N_pad / MD_BN);
   if (gemm_kind(a) == 3) {
     // too few 128 x 128 tiles to fill the chip, enough of 64 x 64 (same bits)

@@ -46,6 +46,7 @@ struct GNode {
   float *Wp = nullptr;         // dense [out][ld(in)] original column order (IBP, spec fold)
   float *Wh = nullptr;         // dense [out][ld(in)] HWC column order when hwc_in (init rows)
   float *Wk = nullptr;         // conv [Co][3][3][Ci]: channels contiguous per tap (init rows)
+  uint16_t *Bs = nullptr, *Ws = nullptr;   // dense: split copies of Bt and of Wh / Wp (see DenseLayer)
   float *b = nullptr;          // bias, zero padded to ld(out) for dense
   std::vector<float> hb;       // host copy of the bias
   int Ci_pad = 0;
@@ -848,7 +849,22 @@ vcr_status graph_load(vcr_ctx *c, const vcr_node *nodes, int32_t n, const int32_
     c->net_bytes += info.size() * sizeof(int32_t);
     HIP_TRY(c, hipMemcpy(g->d_relu_info, info.data(), info.size() * sizeof(int32_t), hipMemcpyHostToDevice));
   }
-  if (dev) HIP_TRY(c, hipDeviceSynchronize());
+  if (dev) {
+    std::vector<SplitItem> items;
+    for (int i = 0; i + 1 < n; ++i) {   // the output node is no product's operand
+      GNode &gn = g->nodes[i];
+      if (gn.op != VCR_DENSE) continue;
+      items.push_back({gn.Bt, gn.ld_out, gn.ld_in, gn.ld_out, &gn.Bs});
+      items.push_back({gn.hwc_in ? gn.Wh : gn.Wp, gn.ld_in, gn.ld_out, gn.ld_in, &gn.Ws});
+    }
+    const vcr_status st = split_operands(c, items);
+    if (st != VCR_OK) return st;
+    const hipError_t e = hipDeviceSynchronize();
+    if (e != hipSuccess) {
+      drop_split_operands(c);
+      return fail(c, VCR_ERR_DEVICE, "hipDeviceSynchronize: %s", hipGetErrorString(e));
+    }
+  }
   destroy_graph(c->graph);
   c->graph = guard.release();
   c->relu_n.clear();
@@ -1092,7 +1108,10 @@ vcr_status run_pass(vcr_ctx *c, GraphNet *g, GBufs &bf, const PassPlan &pp, int 
         ga.A = slot(st.src);
         ga.lda = nd.ld_out;
         ga.Bt = nd.Bt;
+        ga.Bs = nd.Bs;
         ga.ldb = nd.ld_out;
+        ga.N = (int32_t)g->nodes[nd.in0].numel;
+        ga.K_real = (int32_t)nd.numel;
         ga.M = (int32_t)R;
         ga.M_pad = (int32_t)rows_pad(R);
         ga.K = (int32_t)nd.ld_out;
@@ -1197,7 +1216,10 @@ vcr_status run_forward(vcr_ctx *c, GraphNet *g, GBufs &bf, int u0, int units, in
         ga.A = val(f.in);
         ga.lda = nd.ld_in;
         ga.Bt = nd.hwc_in ? nd.Wh : nd.Wp;
+        ga.Bs = nd.Ws;
         ga.ldb = nd.ld_in;
+        ga.N = (int32_t)nd.numel;
+        ga.K_real = (int32_t)g->nodes[nd.in0].numel;
         ga.M = M;
         ga.M_pad = (int32_t)rows_pad(M);
         ga.K = (int32_t)nd.ld_in;

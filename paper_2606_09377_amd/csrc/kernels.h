@@ -43,6 +43,10 @@ struct GemmArgs {
   int32_t K;           // multiple of BK (padded)
   int32_t N_pad;       // multiple of BN
   int32_t mode;        // EpiMode
+  // the same weights split into bf16 parts (split_bf16.h), or null: with them the step runs on
+  // the bf16 matrix cores, over the real columns and contraction length only
+  const uint16_t *Bs;
+  int32_t N, K_real;   // real columns and contraction length (the rest is zero padding)
   // relax epilogue: out = relax(A Bt^T) with the per-unit parameters of the next ReLU
   float *out;
   int64_t ldo;
@@ -79,6 +83,10 @@ struct GemmArgs {
 hipError_t launch_gemm(const GemmArgs &a, hipStream_t s);
 // The kernel launch_gemm runs for these arguments: 0 k_gemm, 2 k_gemm_small, 3 k_gemm_mid.
 int gemm_kind(const GemmArgs &a);
+
+// Split copy (split_bf16.h) of weights src [N][K] of pitch ld: N a multiple of 16, K of 32;
+// dst takes 3 N K values
+hipError_t launch_split_weights(const float *src, int64_t ld, int64_t N, int64_t K, uint16_t *dst, hipStream_t s);
 
 // ---- bandwidth-bound kernels -------------------------------------------------------
 hipError_t launch_fill(float *p, int64_t n, float v, hipStream_t s);

@@ -1,0 +1,119 @@
+// float32 products on the bf16 matrix cores: every float32 operand is the exact sum of three
+// bf16 values (8 significand bits each, 24 in all),
+//   x = h + m + l,  h = bf16(x), m = bf16(x - h), l = x - h - m  (both differences are exact),
+// and a product takes the six of its nine partial products that reach 2^-24 of it,
+//   x y = h h' + (h l' + l h' + m m' + h m' + m h')
+// (the three left out are below 2^-25 together).  h h' and the five small ones are summed in two
+// accumulators, added once at the end.  In one accumulator the small partial products are
+// cut off at the large sum's precision, towards minus infinity: sums over K = 1024 normal
+// products came out 7.6e-8 of the result too low on average (3.3e-6 at K = 65536), and since a
+// bound adds many such sums that bias stayed where rounding errors cancel: bounds were up to 20
+// times as far from 64 bits.  With two accumulators the mean error is 3e-10 (K = 65536: 1.6e-8)
+// and a sum is a third as far off as by the chain of v_mfma_f32_32x32x2f32 it replaces (K =
+// 1024: 1.9e-7 of the result against 5.7e-7; K = 65536: 1.6e-6 against 4.6e-6).
+//
+// Why: the float32 matrix rate of gfx950 is 157 TFLOP/s; six bf16 products run at a sixth of
+// 2.5 PFLOP/s nominal, 305 TFLOP/s of float32 products measured with every operand in
+// registers (the card's power limit sets that rate, not the issue rate).
+//
+// Instruction: v_mfma_f32_16x16x32_bf16, in this order of partial products for every K step of
+// 32 everywhere, so that a result does not depend on which tile size computed it.  The 32x32x16
+// form runs as fast, but a lone wave's chain over K = 1024 takes 5.4 us for its 32 x 32 block
+// against 1.6 us for a 16 x 16 one, and the small launches are such chains.
+#pragma once
+
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+
+namespace vcr {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32v4 __attribute__((ext_vector_type(4)));
+
+// two values at once: the packed pairs of bf16 (element 0 in the low half)
+__device__ __forceinline__ void split_pair(float x0, float x1, uint32_t &h, uint32_t &m, uint32_t &l) {
+  typedef float f32v2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  auto pack = [](float a, float b) {   // v_cvt_pk_bf16_f32, round to nearest even
+    const f32v2 v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+  };
+  auto lo = [](uint32_t u) { return __builtin_bit_cast(float, u << 16); };
+  auto hi = [](uint32_t u) { return __builtin_bit_cast(float, u & 0xffff0000u); };
+  h = pack(x0, x1);
+  x0 -= lo(h);
+  x1 -= hi(h);
+  m = pack(x0, x1);
+  x0 -= lo(m);
+  x1 -= hi(m);
+  l = pack(x0, x1);
+}
+
+// the three bf16 operands of eight consecutive float32 values
+struct Split8 {
+  bf16x8 h, m, l;
+};
+__device__ __forceinline__ Split8 split8(f32v4 x, f32v4 y) {
+  typedef uint32_t u32v4 __attribute__((ext_vector_type(4)));
+  u32v4 h, m, l;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    uint32_t a, b, c;
+    split_pair(q < 2 ? x[2 * q] : y[2 * q - 4], q < 2 ? x[2 * q + 1] : y[2 * q - 3], a, b, c);
+    h[q] = a;
+    m[q] = b;
+    l[q] = c;
+  }
+  return {__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
+}
+
+// |w| of a split operand (mask 0x80008000; w itself with mask 0): the sign of w is h's, and the
+// three parts change sign together
+__device__ __forceinline__ Split8 split_abs(Split8 w, uint32_t mask) {
+  typedef uint32_t u32v4 __attribute__((ext_vector_type(4)));
+  const u32v4 h = __builtin_bit_cast(u32v4, w.h);
+  const u32v4 s = h & mask;
+  return {__builtin_bit_cast(bf16x8, h ^ s), __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32v4, w.m) ^ s),
+          __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32v4, w.l) ^ s)};
+}
+
+// acc += W A^T over 32 k: 16 weight rows (the accumulator's rows) and 16 coefficient rows (its
+// columns).  Lane (r = lane % 16, g = lane / 16) holds k = 8 g .. 8 g + 7 of row r of both
+// operands, and of the result column r, rows 4 g .. 4 g + 3: a lane ends with four consecutive
+// output columns of one coefficient row.
+__device__ __forceinline__ f32v4 mfma_bf16(bf16x8 w, bf16x8 a, f32v4 acc) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, a, acc, 0, 0, 0);
+}
+// One column block of a wave's MB row blocks: hi takes h h', lo the small partial products
+template <int MB, int NB>
+__device__ __forceinline__ void split_mma(const Split8 (&a)[MB], const Split8 &w, f32v4 (&hi)[MB][NB],
+                                          f32v4 (&lo)[MB][NB], int j) {
+#pragma unroll
+  for (int i = 0; i < MB; ++i) lo[i][j] = mfma_bf16(w.l, a[i].h, lo[i][j]);
+#pragma unroll
+  for (int i = 0; i < MB; ++i) hi[i][j] = mfma_bf16(w.h, a[i].h, hi[i][j]);
+#pragma unroll
+  for (int i = 0; i < MB; ++i) lo[i][j] = mfma_bf16(w.h, a[i].l, lo[i][j]);
+#pragma unroll
+  for (int i = 0; i < MB; ++i) lo[i][j] = mfma_bf16(w.m, a[i].m, lo[i][j]);
+#pragma unroll
+  for (int i = 0; i < MB; ++i) lo[i][j] = mfma_bf16(w.m, a[i].h, lo[i][j]);
+#pragma unroll
+  for (int i = 0; i < MB; ++i) lo[i][j] = mfma_bf16(w.h, a[i].m, lo[i][j]);
+}
+__device__ __forceinline__ void split_mma1(const Split8 &a, const Split8 &w, f32v4 &hi, f32v4 &lo) {
+  lo = mfma_bf16(w.l, a.h, lo);
+  hi = mfma_bf16(w.h, a.h, hi);
+  lo = mfma_bf16(w.h, a.l, lo);
+  lo = mfma_bf16(w.m, a.m, lo);
+  lo = mfma_bf16(w.m, a.h, lo);
+  lo = mfma_bf16(w.h, a.m, lo);
+}
+
+// Layout of a split weight operand of N rows and K columns (N a multiple of 16, K of 32), in
+// the order the instruction reads it: [N / 16][K / 32][h, m, l][64 lanes][8 k].  One (block,
+// K step, part) is 1 KB, loaded by one wave-wide 16-byte load and read from LDS at 16 bytes a
+// lane without bank conflicts.
+constexpr int SPLIT_BLOCK = 3 * 64 * 8;   // bf16 values of one 16 x 32 block
+
+}  // namespace vcr
