@@ -17,8 +17,8 @@ namespace vcr {
 
 // The tile shapes, by launch size; every shape gives the same bits.
 //   SplitL  128 x 128, 4 waves of 64 x 64, two stages of 40 KB: two workgroups per compute unit
-//   SplitM  64 x 64, 4 waves of 32 x 32
-//   SplitS  32 x 64, 8 waves of 16 x 16
+//   SplitM  64 x 64, 4 waves of 16 x 64
+//   SplitS  32 x 64, 4 waves of 16 x 32
 template <int BM_, int BN_, int WM_, int WN_, int NS_, int MINB_>
 struct SplitTile {
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, NS = NS_, MINB = MINB_;
@@ -28,8 +28,8 @@ struct SplitTile {
   static constexpr int LDS_FLOATS = NS * (A_FLOATS + B_FLOATS);
 };
 typedef SplitTile<128, 128, 2, 2, 2, 2> SplitL;
-typedef SplitTile<64, 64, 2, 2, 2, 2> SplitM;
-typedef SplitTile<32, 64, 2, 4, 3, 2> SplitS;
+typedef SplitTile<64, 64, 4, 1, 2, 2> SplitM;
+typedef SplitTile<32, 64, 2, 2, 2, 2> SplitS;
 
 // Parameters of four consecutive columns for one coefficient row, with the row's split neuron
 // (if any) replaced.  flags: the tile's split table (four entries of the row's domain), or null
@@ -353,12 +353,16 @@ static hipError_t launch_split_tile(const GemmArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// 0: SplitL, 3: SplitM, 2: SplitS
+// 0: SplitL, 3: SplitM, 2: SplitS.  In its own loop (K = 1024, N = 1024) SplitL reaches 228
+// TFLOP/s and SplitM 187; SplitL holds 512 workgroups on the chip at once, so it runs where its
+// rounds of 512 are full enough to keep that lead.  SplitM overtakes SplitS between 256 tiles
+// (64 x 64; 158 us against 131 at K = 8192) and 512 (29 us against 32 at K = 1024).
 static int split_kind(const GemmArgs &a) {
   const int64_t big = (int64_t)((a.M + 127) / 128) * (a.N_pad / 128);
+  const int64_t rounds = (big + 511) / 512;
+  if (big >= 512 && big * 100 >= rounds * 512 * 82) return 0;
   const int64_t mid = (int64_t)((a.M + 63) / 64) * (a.N_pad / 64);
-  if (big >= 640) return 0;
-  return mid >= 128 ? 3 : 2;
+  return mid > 384 ? 3 : 2;
 }
 
 }  // namespace vcr
