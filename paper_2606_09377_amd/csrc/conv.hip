@@ -48,7 +48,10 @@ __device__ __forceinline__ uint32_t fdiv(uint32_t n, FastDiv d) {
 }
 
 // floor(a / b) for b > 0 and any sign of a
-__host__ __device__ inline int floor_div(int a, int b) { return a >= 0 ? a / b : -((-a + b - 1) / b); }
+__host__ __device__ inline int floor_div(int a, int b) {
+  if (b <= 2) return a >> (b - 1);   // the steps of the strides built here: no division
+  return a >= 0 ? a / b : -((-a + b - 1) / b);
+}
 
 // Class positions i in [0, n) of one axis whose image coordinate o + u0 + ustep i lies in
 // [0, H): the interval [*lo, *hi) (empty: *lo == *hi)
@@ -467,6 +470,12 @@ __global__ __launch_bounds__(256, MINB) void k_convt(const ConvTArgs p) {
   convt_epilogue<BM, BN, WM, WN, RELU, AL, SPL>(p, cl, tab, acc, m0, n0, nt, &As[0][0]);
 }
 
+}  // namespace vcr
+
+#include "conv_split.h"
+
+namespace vcr {
+
 // Classes of one axis: positions u of the destination window with the same taps ky, as an
 // arithmetic progression of positions and of taps.
 struct AxisClass {
@@ -651,6 +660,13 @@ hipError_t launch_convt_part(const ConvTArgs &a0, int part, hipStream_t s) {
   if (al && (!a.alpha || !a.pre || !a.P_pos || !a.dense)) return hipErrorInvalidValue;
   if (spl && (!a.P_pos || !a.dense || a.splits.rows_per_domain <= 0)) return hipErrorInvalidValue;
   const dim3 blk256(256);
+  if (a.Bs && a.S_in <= 256 && a.Ha <= 256) {    // split operands: whole cache lines of 32 channels
+    if (a.row_stride_out % 4 || a.row_stride_in % 4 || a.res_row_stride % 4 || a.C_in % 16) return hipErrorInvalidValue;
+    const bool wide = a.N_pad % 128 == 0;
+    const int64_t blk = convt_fill(a, cu, d, CS_BM, wide ? 128 : 64);
+    if (blk < 0) return hipErrorInvalidValue;
+    return wide ? launch_convt_split<2>(a, blk, s) : launch_convt_split<1>(a, blk, s);
+  }
   if (a.N_pad % 128 == 0) {   // 128 x 128 tiles, 2 x 2 waves of 64 x 64
     const int64_t blk = convt_fill(a, cu, d, 128, 128);
     if (blk < 0) return hipErrorInvalidValue;

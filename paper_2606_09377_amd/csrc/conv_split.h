@@ -1,0 +1,316 @@
+// The transposed convolution and the gradient pass's forward convolution on split operands
+// (split_bf16.h), run when the layer's split weights are present.  Part of conv.hip.
+//
+// The same implicit GEMMs as k_convt and k_fwd_conv (rows, position classes, taps, epilogues),
+// with K steps of 32 channels of one tap: a step gathers 128 contiguous bytes of each of the
+// tile's 96 source positions (one cache line, where the 16-channel steps of the float32 kernels
+// read two halves) and the weights' three parts, straight into double-buffered LDS.  Three waves
+// of 32 x 64 share a 64-column tile (53 KB: three workgroups per compute unit), six a 128-column
+// one (77 KB: two).  The tile is that small for the sake of those workgroups: on the 3 x 32 x 32
+// ResNet a 128-row tile (two workgroups) spends 19 us in its K loop, at 233 TFLOP/s, and as much
+// before and after it, which only other workgroups' K loops can hide.
+#pragma once
+
+#include "split_bf16.h"
+
+namespace vcr {
+
+constexpr int CS_BM = 96;   // GEMM rows per workgroup
+template <int WN>
+struct ConvSplit {
+  static constexpr int WM = CS_BM / 32, NW = WM * WN, T = 64 * NW, BN = 64 * WN;
+  static constexpr int MB = 2, NB = 4;                       // a wave: 32 rows x 64 columns
+  static constexpr int A_FLOATS = CS_BM * 32, B_FLOATS = BN / 16 * SPLIT_BLOCK / 2;
+  static constexpr int AQ = CS_BM / 8 / NW, BQ = 3 * (BN / 16) / NW;   // loads of a wave per K step
+  static_assert(CS_BM / 8 % NW == 0 && 3 * (BN / 16) % NW == 0, "loads spread evenly over the waves");
+};
+
+// Four consecutive channels of one destination position: the split neurons of the row's domain
+// among them (their relaxation replaces prm; ent, sterm as in split_override)
+__device__ __forceinline__ void split_override4(const SplitTable &st, int row, int relu, int n, float4 (&prm)[4],
+                                                int (&ent)[4], float (&sterm)[4]) {
+  int d = row / st.rows_per_domain;
+  d = d < st.D ? d : st.D - 1;
+  const int e0 = st.off[d * (st.R + 1) + relu];
+  const int e1 = st.off[d * (st.R + 1) + relu + 1];
+  for (int e = e0; e < e1; ++e) {
+    const int v = st.ent_n[d * st.S + e] - n;
+    if (v < 0 || v > 3) continue;
+    const float4 q = st.ent_p[d * st.S + e];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      if (k == v) {
+        prm[k] = make_float4(q.x, q.y, q.z, prm[k].w);
+        ent[k] = e;
+        sterm[k] = q.w;
+      }
+  }
+}
+
+// What the epilogue needs of a tile row, computed once per workgroup while the first K step is
+// in flight: output and residual offsets (residual -1: none), parameter offset (-1 outside the
+// image), partial-sum index (-1 past the last row) and coefficient row.
+struct ConvRows {
+  int64_t ob[CS_BM], rb[CS_BM];
+  int pb[CS_BM], mo[CS_BM], r[CS_BM];
+  uint32_t yx[CS_BM];   // iy, ix, anchor y, anchor x, a byte each
+};
+
+__device__ __forceinline__ void conv_row_info(const ConvTArgs &p, const ConvClass &cl, ConvRows &rows, int m0, int tr) {
+  const bool valid = m0 + tr < cl.M;
+  const int r = rows.r[tr];
+  const uint32_t yx = rows.yx[tr];
+  const int u = cl.u0 + (int)(yx & 255) * cl.ustep;
+  const int w = cl.w0 + (int)((yx >> 8) & 255) * cl.wstep;
+  const int4 an = p.rows[r];   // (unit, anchor y, anchor x, -)
+  const int gy = p.dense ? u : an.y * p.scale - p.h_in + u;
+  const int gx = p.dense ? w : an.z * p.scale - p.h_in + w;
+  const bool inside = valid && gy >= 0 && gx >= 0 && gy < p.H_in && gx < p.H_in;
+  const int du = u - p.res_off, dw = w - p.res_off;
+  rows.mo[tr] = valid ? r * (p.S_in * p.S_in) + u * p.S_in + w : -1;
+  rows.ob[tr] = (int64_t)r * p.row_stride_in + ((int64_t)u * p.S_in + w) * p.C_in;
+  rows.pb[tr] = inside ? ((an.x * p.H_in + gy) * p.H_in + gx) * p.C_in : -1;
+  rows.rb[tr] = inside && p.res && du >= 0 && dw >= 0 && du < p.res_S && dw < p.res_S
+                    ? (int64_t)r * p.res_row_stride + ((int64_t)du * p.res_S + dw) * p.C_in
+                    : -1;
+}
+
+// Epilogue of the transposed convolution (see convt_epilogue): a lane holds, of GEMM rows
+// 16 i + lane % 16 of its wave, channels 16 j + 4 (lane / 16) .. + 3.  The relaxation parameters
+// or residuals are loaded four blocks ahead: with one block ahead the eight blocks of a wave
+// were eight waits on the L2.
+template <int WN, bool RELU, bool AL, bool SPL>
+__device__ __forceinline__ void convt_split_epilogue(const ConvTArgs &p, const f32v4 (&acc)[2][4], const ConvRows &rows,
+                                                     int n0, int nt, int wm, int wn, int nj) {
+  typedef ConvSplit<WN> CS;
+  constexpr int MB = CS::MB, NB = CS::NB;
+  const int lane = threadIdx.x & 63, r16 = lane & 15, g4 = lane >> 4;
+  const float4 *__restrict__ Pp = p.P_pos;
+  const float *__restrict__ resp = p.res;
+  float *__restrict__ outp = p.out;
+  const float *__restrict__ alp = p.alpha;
+  float *__restrict__ prep = p.pre;
+  const int nw = n0 + wn * 64 + 4 * g4;   // the lane's first channel
+  const int lr0 = wm * 32 + r16;
+  float4 prm[NB][4];
+  f32v4 rv[NB];
+  // positions outside the image read parameter 0 (it meets a zero coefficient)
+  auto fetch = [&](int i, int j) {
+    const int lr = lr0 + i * 16, n = nw + j * 16;
+    if constexpr (RELU) {
+      const uint32_t off = rows.pb[lr] >= 0 ? (uint32_t)(rows.pb[lr] + n) : 0u;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) prm[j][v] = Pp[off + v];
+    }
+    rv[j] = f32v4{0.f, 0.f, 0.f, 0.f};
+    if (resp) rv[j] = *reinterpret_cast<const f32v4 *>(rows.rb[lr] >= 0 ? resp + rows.rb[lr] + n : g_zero4);
+  };
+#pragma unroll
+  for (int j = 0; j < NB; ++j)
+    if (j < nj) fetch(0, j);
+#pragma unroll
+  for (int i = 0; i < MB; ++i) {
+    const int lr = lr0 + i * 16;
+    const int pb = rows.pb[lr], mo = rows.mo[lr], rr = rows.r[lr];
+    const int64_t ob = rows.ob[lr];
+    float x = 0.f;
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      if (j >= nj) continue;   // columns past C_in
+      const int n = nw + j * 16;
+      const f32v4 a = acc[i][j] + rv[j];
+      float4 pr[4] = {prm[j][0], prm[j][1], prm[j][2], prm[j][3]};
+      if (i + 1 < MB) fetch(i + 1, j);
+      f32v4 o = {0.f, 0.f, 0.f, 0.f};
+      if (pb >= 0) {   // inside the image: relax (or identity) and constant terms
+        if constexpr (RELU) {
+          int ent[4] = {-1, -1, -1, -1};
+          float sterm[4] = {0.f, 0.f, 0.f, 0.f};
+          if constexpr (SPL) {   // subdomains: a split neuron's clamped relaxation
+            if (mo >= 0) split_override4(p.splits, rr, p.relu_index, pb + n, pr, ent, sterm);
+          }
+          f32v4 al = {0.f, 0.f, 0.f, 0.f};
+          if constexpr (AL) {   // alpha-CROWN: the row's own slopes at unstable neurons; the
+                                // coefficients before relaxation are recorded (the gradient pass
+                                // uses them at unstable neurons only)
+            if (mo >= 0 && fmaxf(fmaxf(pr[0].z, pr[1].z), fmaxf(pr[2].z, pr[3].z)) > 0.f) {
+              al = *reinterpret_cast<const f32v4 *>(alp + ob + n);
+              *reinterpret_cast<f32v4 *>(prep + ob + n) = a;
+            }
+          }
+          float xb = 0.f;
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const float lam = AL && pr[v].z > 0.f ? al[v] : pr[v].x;
+            float ap = a[v] > 0.f ? a[v] * lam : a[v] * pr[v].y;
+            if constexpr (SPL) {   // beta-CROWN: the split's multiplier term
+              if (ent[v] >= 0 && p.splits.beta)
+                ap = fmaf(p.splits.beta[(int64_t)rr * p.splits.S + ent[v]], sterm[v], ap);
+            }
+            o[v] = ap;
+            xb += fmaf(ap, pr[v].w, fminf(a[v], 0.f) * pr[v].z);
+          }
+          x += xb;
+        } else {
+          const float4 bn = *reinterpret_cast<const float4 *>(p.bias + n);
+          o = a;
+          x += fmaf(a[3], bn.w, fmaf(a[2], bn.z, fmaf(a[1], bn.y, a[0] * bn.x)));
+        }
+      }
+      // (ordinary stores: a lane's 16 bytes and its three neighbours' make half a line, and the
+      // cache joins the halves of blocks j and j + 1; non-temporal ones measured 3% slower)
+      if (mo >= 0) *reinterpret_cast<f32v4 *>(outp + ob + n) = o;
+    }
+    x += __shfl_xor(x, 16);
+    x += __shfl_xor(x, 32);
+    if (g4 == 0 && mo >= 0) p.part[(int64_t)(nt * WN + wn) * p.M_pad + mo] = x;
+  }
+}
+
+template <int WN, bool RELU, bool AL, bool SPL>
+__global__ __launch_bounds__(ConvSplit<WN>::T, 3) void k_convt_split(const ConvTArgs p) {
+  typedef ConvSplit<WN> CS;
+  constexpr int MB = CS::MB, NB = CS::NB;
+  __shared__ __attribute__((aligned(16))) float lds[2 * (CS::A_FLOATS + CS::B_FLOATS)];
+  __shared__ ClipTab tab;
+  __shared__ ConvRows rows;
+  float *As = lds, *Bs = lds + 2 * CS::A_FLOATS;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave % CS::WM, wn = wave / CS::WM;
+
+  // class of this workgroup (wave-uniform selects, no indexed argument access)
+  const int bid = blockIdx.x;
+  const int c = (bid >= p.cls[1].blk0) + (bid >= p.cls[2].blk0) + (bid >= p.cls[3].blk0);
+  const ConvClass cl = c == 0 ? p.cls[0] : c == 1 ? p.cls[1] : c == 2 ? p.cls[2] : p.cls[3];
+  const int n_nt = p.N_pad / CS::BN;
+  const int lb = bid - cl.blk0;
+  const int mt = lb / n_nt, nt = lb - mt * n_nt;
+  const int m0 = mt * CS_BM, n0 = nt * CS::BN;
+  const int sh = p.stride == 2 ? 1 : 0;
+  const int nj = min(max((p.C_in - (n0 + wn * 64) + 15) / 16, 0), NB);   // column blocks with real channels
+  if (cl.clip) {   // workgroup-uniform
+    if (wave == 0) clip_tables(p, cl, tab, lane);
+    __syncthreads();
+  }
+
+  // the tile's rows decoded once, a row per thread (the clipped decode is a chain of dependent
+  // LDS reads)
+  if (tid < CS_BM) {
+    const uint32_t m = (uint32_t)(m0 + tid);
+    uint32_t r = 0;
+    int iy = 0, ix = 0, anc = 0;
+    if (m < (uint32_t)cl.M) convt_row(p, cl, tab, m, &r, &iy, &ix, &anc);
+    const int ay = p.src_scale > 0 ? anc / p.Ha : 0, ax = p.src_scale > 0 ? anc - ay * p.Ha : 0;
+    rows.r[tid] = (int)r;
+    rows.yx[tid] = (uint32_t)iy | (uint32_t)ix << 8 | (uint32_t)ay << 16 | (uint32_t)ax << 24;
+  }
+  __syncthreads();
+
+  // Per load of this wave: 8 tile rows, a row's 8 chunks of 16 bytes over 8 lanes, the chunk a
+  // lane fetches being the one lds_swz puts into its slot.  Of each row the address of its
+  // position under a zero shift, and a bit per tap row and tap column of the class: whether the
+  // tap's source position lies inside the source window and, of a windowed source, inside the
+  // image.  Tap (ty, tx) then reads the address plus a wave-uniform offset, or a zero block.
+  // (No division by the class's tap counts here or in the K loop: a division is some 30 vector
+  // instructions, and nine of them a row cost more than the whole first K step.)
+  auto shift_y = [&](int ty) { return (cl.u0 + p.delta - (cl.ky0 + cl.kys * ty)) >> sh; };   // exact
+  auto shift_x = [&](int tx) { return (cl.w0 + p.delta - (cl.kx0 + cl.kxs * tx)) >> sh; };
+  const float *a_row[CS::AQ];
+  uint32_t ty_ok[CS::AQ], tx_ok[CS::AQ];
+#pragma unroll
+  for (int q = 0; q < CS::AQ; ++q) {
+    const int row = (q * CS::NW + wave) * 8 + (lane >> 3);
+    const uint32_t yx = rows.yx[row];
+    const int iy = (int)(yx & 255), ix = (int)((yx >> 8) & 255);
+    int ylo = 0, xlo = 0, yhi = p.S_out, xhi = p.S_out;
+    if (p.src_scale > 0) {   // windowed source (Ha > 0)
+      const int oy = (int)((yx >> 16) & 255) * p.src_scale - p.src_h, ox = (int)(yx >> 24) * p.src_scale - p.src_h;
+      ylo = max(0, -oy);
+      xlo = max(0, -ox);
+      yhi = min(p.S_out, p.H_out - oy);
+      xhi = min(p.S_out, p.H_out - ox);
+    }
+    a_row[q] = p.A + (int64_t)rows.r[row] * p.row_stride_out + ((int64_t)iy * p.S_out + ix) * p.C_out +
+               ((lane & 7) ^ lds_swz<32>(row)) * 4;
+    ty_ok[q] = tx_ok[q] = 0;
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      const int y = iy + shift_y(t), x = ix + shift_x(t);
+      ty_ok[q] |= (uint32_t)(y >= ylo && y < yhi) << t;
+      tx_ok[q] |= (uint32_t)(x >= xlo && x < xhi) << t;
+    }
+    if (m0 + row >= cl.M) ty_ok[q] = 0;
+  }
+  // K order: channel blocks outer, taps inner: the shifted re-reads of one source block follow
+  // each other (they hit the caches instead of HBM)
+  const int cpt = p.C_out / 32;
+  int l_ty = 0, l_tx = 0, l_cb = 0;   // the next step to load
+  auto gload = [&](int buf) {
+    const int64_t off = ((int64_t)shift_y(l_ty) * p.S_out + shift_x(l_tx)) * p.C_out + l_cb * 32;
+#pragma unroll
+    for (int q = 0; q < CS::AQ; ++q) {
+      const float *src = (ty_ok[q] >> l_ty) & (tx_ok[q] >> l_tx) & 1 ? a_row[q] + off : g_zero4;
+      dma16(src, As + buf * CS::A_FLOATS + (q * CS::NW + wave) * 256);
+    }
+    const int kb = (3 * (cl.ky0 + cl.kys * l_ty) + cl.kx0 + cl.kxs * l_tx) * cpt + l_cb;
+#pragma unroll
+    for (int q = 0; q < CS::BQ; ++q) {
+      const int i = q * CS::NW + wave, nb = i / 3, part = i - 3 * nb;
+      dma16(p.Bs + ((int64_t)(n0 / 16 + nb) * (9 * cpt) + kb) * SPLIT_BLOCK + part * 512, (uint32_t)lane * 16,
+            Bs + buf * CS::B_FLOATS + i * 256);
+    }
+    if (++l_tx == cl.ntx) {
+      l_tx = 0;
+      if (++l_ty == cl.nty) {
+        l_ty = 0;
+        ++l_cb;
+      }
+    }
+  };
+
+  f32v4 hi[MB][NB], lo[MB][NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) hi[i][j] = lo[i][j] = f32v4{0.f, 0.f, 0.f, 0.f};
+  const int KT = cl.nty * cl.ntx * cpt;
+  const int r16 = lane & 15, g4 = lane >> 4, sw = lds_swz<32>(r16);
+  const int ch0 = ((2 * g4) ^ sw) * 4, ch1 = ((2 * g4 + 1) ^ sw) * 4;
+  gload(0);
+  if (tid < CS_BM) conv_row_info(p, cl, rows, m0, tid);   // read after the loop's barriers
+  for (int kt = 0; kt < KT; ++kt) {
+    const int cur = kt & 1;
+    wait_vmcnt<0>();   // this wave's part of step kt has landed
+    barrier_only();    // every wave's has, and step kt - 1's stage is free
+    if (kt + 1 < KT) gload(cur ^ 1);
+    split_step<MB, NB, false>(As + cur * CS::A_FLOATS + (wm * 32 + r16) * 32, ch0, ch1,
+                              reinterpret_cast<const bf16x8 *>(Bs + cur * CS::B_FLOATS) + wn * NB * 192 + lane, nj, 0u,
+                              hi, lo);
+  }
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) hi[i][j] += lo[i][j];
+  convt_split_epilogue<WN, RELU, AL, SPL>(p, hi, rows, n0, nt, wm, wn, nj);
+}
+
+template <int WN>
+static hipError_t launch_convt_split(const ConvTArgs &a, int64_t blk, hipStream_t s) {
+  const bool al = a.alpha || a.pre, spl = a.splits.D > 0;
+  const dim3 g((unsigned)blk), t(ConvSplit<WN>::T);
+  if (blk <= 0) return hipSuccess;
+  if (al && spl)
+    hipLaunchKernelGGL((k_convt_split<WN, true, true, true>), g, t, 0, s, a);
+  else if (spl)
+    hipLaunchKernelGGL((k_convt_split<WN, true, false, true>), g, t, 0, s, a);
+  else if (al)
+    hipLaunchKernelGGL((k_convt_split<WN, true, true, false>), g, t, 0, s, a);
+  else if (a.P_pos)
+    hipLaunchKernelGGL((k_convt_split<WN, true, false, false>), g, t, 0, s, a);
+  else
+    hipLaunchKernelGGL((k_convt_split<WN, false, false, false>), g, t, 0, s, a);
+  return hipGetLastError();
+}
+
+}  // namespace vcr

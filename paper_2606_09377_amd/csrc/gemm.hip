@@ -601,7 +601,7 @@ namespace vcr {
 
 int gemm_kind(const GemmArgs &a) {
   if (a.M_pad <= 0 || a.N_pad <= 0) return 0;
-  if (a.Bs) return split_kind(a);
+  if (use_split(a)) return split_kind(a);
   const int64_t grid = (int64_t)(a.M_pad / BM) * (a.N_pad / BN);
   const int64_t mid = (int64_t)(a.M_pad / MD_BM) * (a.N_pad / MD_BN);
   const int64_t last = grid % GEMM_ROUND;
@@ -626,7 +626,7 @@ hipError_t launch_gemm(const GemmArgs &a, hipStream_t s) {
   const bool al = a.alpha || a.pre;
   if (a.mode != EPI_RELAX && a.mode != EPI_CONCRETIZE && a.mode != EPI_FORWARD && a.mode != EPI_AFFINE)
     return hipErrorInvalidValue;
-  if (a.Bs) {
+  if (use_split(a)) {
     if (a.M <= 0 || a.M > a.M_pad || a.N <= 0 || a.N > a.N_pad || a.K_real <= 0 || a.K_real > a.K || a.lda % 4 || ld % 4)
       return hipErrorInvalidValue;
     switch (gemm_kind(a)) {

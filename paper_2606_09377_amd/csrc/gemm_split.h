@@ -231,20 +231,25 @@ __global__ __launch_bounds__(TS::T, TS::MINB) void k_gemm_split(const GemmArgs p
   constexpr int AQ = (AI + NW - 1) / NW, BQ = (BI + NW - 1) / NW;
   static_assert(AI % NW == 0 || AI < NW, "loads spread evenly over the waves");
   const int kblocks = p.K / 32;
+  uint32_t a_off[AQ];   // bytes from the tile's first row, under 2^32 (use_split)
+#pragma unroll
+  for (int q = 0; q < AQ; ++q) {
+    const int row = (AI < NW ? wave % AI : q * NW + wave) * 8 + (lane >> 3);
+    a_off[q] = (uint32_t)row * (uint32_t)(p.lda * 4) + ((lane & 7) ^ lds_swz<32>(row)) * 16;
+  }
+  const float *a_tile = p.A + (int64_t)m0 * p.lda;
+  const uint16_t *b_tile = p.Bs + (int64_t)(n0 / 16) * kblocks * SPLIT_BLOCK;
   auto issue = [&](int kt, int buf) {
 #pragma unroll
     for (int q = 0; q < AQ; ++q) {
       const int i = AI < NW ? wave % AI : q * NW + wave;   // fewer loads than waves: some repeat one
-      const int row = i * 8 + (lane >> 3);
-      const int chunk = (lane & 7) ^ lds_swz<32>(row);
-      dma16(p.A + (int64_t)(m0 + row) * p.lda + kt * 32 + chunk * 4, As + buf * TS::A_FLOATS + i * 256);
+      dma16(a_tile + kt * 32, a_off[q], As + buf * TS::A_FLOATS + i * 256);
     }
 #pragma unroll
     for (int q = 0; q < BQ; ++q) {
       const int i = min(q * NW + wave, BI - 1);
       const int nb = i / 3, part = i - 3 * nb;
-      const int64_t blk = (int64_t)(n0 / 16 + nb) * kblocks + kt;
-      dma16(reinterpret_cast<const float *>(p.Bs + blk * SPLIT_BLOCK + part * 512 + lane * 8),
+      dma16(b_tile + ((int64_t)nb * kblocks + kt) * SPLIT_BLOCK + part * 512, (uint32_t)lane * 16,
             Bs + buf * TS::B_FLOATS + i * 256);
     }
   };
@@ -272,36 +277,7 @@ __global__ __launch_bounds__(TS::T, TS::MINB) void k_gemm_split(const GemmArgs p
     if (kt + NS - 1 < KT) issue(kt + NS - 1, cur + NS - 1 >= NS ? cur - 1 : cur + NS - 1);
     const float *as = As + cur * TS::A_FLOATS + (wm * (TS::BM / TS::WM) + r16) * 32;
     const bf16x8 *bs = reinterpret_cast<const bf16x8 *>(Bs + cur * TS::B_FLOATS) + wn * NB * 192 + lane;
-    auto load_w = [&](int j) {
-      const Split8 w{bs[j * 192], bs[j * 192 + 64], bs[j * 192 + 128]};
-      return AFF ? split_abs(w, abs_mask) : w;
-    };
-    f32v4 x[MB], y[MB];
-#pragma unroll
-    for (int i = 0; i < MB; ++i) {
-      x[i] = *reinterpret_cast<const f32v4 *>(as + i * 512 + ch0);
-      y[i] = *reinterpret_cast<const f32v4 *>(as + i * 512 + ch1);
-    }
-    Split8 a[MB], w[2];
-    w[0] = load_w(0);
-    // the first column block multiplies each row block as soon as it is split; every block's
-    // weights are read from LDS while the block before is multiplied
-#pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      if (j < nj) {
-        if (j + 1 < NB) w[(j + 1) & 1] = load_w(j + 1);
-        if (j == 0) {
-#pragma unroll
-          for (int i = 0; i < MB; ++i) {
-            a[i] = split8(x[i], y[i]);
-            split_mma1(a[i], w[0], hi[i][0], lo[i][0]);
-          }
-        } else {
-          split_mma<MB, NB>(a, w[j & 1], hi, lo, j);
-        }
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
+    split_step<MB, NB, AFF>(as, ch0, ch1, bs, nj, abs_mask, hi, lo);
     cur = cur + 1 == NS ? 0 : cur + 1;
   }
 #pragma unroll
@@ -352,6 +328,9 @@ static hipError_t launch_split_tile(const GemmArgs &a, hipStream_t s) {
     hipLaunchKernelGGL((k_gemm_split<TS, false, false, false>), g, t, 0, s, a);
   return hipGetLastError();
 }
+
+// The split kernels address a tile of coefficient rows by 32-bit byte offsets.
+static bool use_split(const GemmArgs &a) { return a.Bs && a.lda <= (int64_t)1 << 23; }
 
 // 0: SplitL, 3: SplitM, 2: SplitS.  In its own loop (K = 1024, N = 1024) SplitL reaches 228
 // TFLOP/s and SplitM 187; SplitL holds 512 workgroups on the chip at once, so it runs where its

@@ -46,7 +46,8 @@ struct GNode {
   float *Wp = nullptr;         // dense [out][ld(in)] original column order (IBP, spec fold)
   float *Wh = nullptr;         // dense [out][ld(in)] HWC column order when hwc_in (init rows)
   float *Wk = nullptr;         // conv [Co][3][3][Ci]: channels contiguous per tap (init rows)
-  uint16_t *Bs = nullptr, *Ws = nullptr;   // dense: split copies of Bt and of Wh / Wp (see DenseLayer)
+  // split copies (see DenseLayer) of Bt, and of Wh / Wp (dense) or Wk (conv)
+  uint16_t *Bs = nullptr, *Ws = nullptr;
   float *b = nullptr;          // bias, zero padded to ld(out) for dense
   std::vector<float> hb;       // host copy of the bias
   int Ci_pad = 0;
@@ -853,6 +854,8 @@ vcr_status graph_load(vcr_ctx *c, const vcr_node *nodes, int32_t n, const int32_
     std::vector<SplitItem> items;
     for (int i = 0; i + 1 < n; ++i) {   // the output node is no product's operand
       GNode &gn = g->nodes[i];
+      if (gn.op == VCR_CONV2D && gn.Ci % 32 == 0 && gn.C % 32 == 0)   // not the stem
+        items.push_back({gn.Bt, 9 * (int64_t)gn.C, gn.Ci_pad, 9 * (int64_t)gn.C, &gn.Bs});
       if (gn.op != VCR_DENSE) continue;
       items.push_back({gn.Bt, gn.ld_out, gn.ld_in, gn.ld_out, &gn.Bs});
       items.push_back({gn.hwc_in ? gn.Wh : gn.Wp, gn.ld_in, gn.ld_out, gn.ld_in, &gn.Ws});
@@ -1009,6 +1012,7 @@ vcr_status run_pass(vcr_ctx *c, GraphNet *g, GBufs &bf, const PassPlan &pp, int 
         a.C_out = nd.C;
         a.Bt = nd.Bt;
         a.ldb = 9 * (int64_t)nd.C;
+        a.Bs = nd.Bs;
         a.N_pad = nd.Ci_pad;
         a.C_in = nd.Ci;
         a.S_in = st.dst.S();

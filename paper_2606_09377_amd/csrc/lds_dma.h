@@ -57,6 +57,21 @@ __device__ __forceinline__ void dma16(const float *g, float *lds) {
       : "s"(__builtin_amdgcn_readfirstlane(l)), "v"(g)
       : "memory", "m0");
 }
+// The same from a wave-uniform base and a 32-bit byte offset per lane: no vector instruction
+// forms the address.
+__device__ __forceinline__ void dma16(const void *base, uint32_t byte_off, float *lds) {
+  const uint32_t l = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float *)lds;
+  const uint64_t b = (uint64_t)(uintptr_t)base;
+  const uint64_t ub = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)b) |
+                      (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(b >> 32)) << 32;
+  asm volatile(
+      "s_mov_b32 m0, %0\n\t"
+      "s_nop 0\n\t"
+      "global_load_lds_dwordx4 %1, %2"
+      :
+      : "s"(__builtin_amdgcn_readfirstlane(l)), "v"(byte_off), "s"(ub)
+      : "memory", "m0");
+}
 #pragma clang diagnostic pop
 
 // Workgroup barrier after this wave's LDS reads have completed, without the memory fences of

@@ -116,4 +116,42 @@ __device__ __forceinline__ void split_mma1(const Split8 &a, const Split8 &w, f32
 // lane without bank conflicts.
 constexpr int SPLIT_BLOCK = 3 * 64 * 8;   // bf16 values of one 16 x 32 block
 
+// One K step of a wave from LDS: MB row blocks of coefficients (as: the lane's first row, 32
+// floats a row, 16 rows a block, the lane's two 16-byte chunks at ch0 and ch1) times NB column
+// blocks of weights (ws: the lane's part of the first block), the first nj of which hold real
+// columns (wave-uniform).  The first column block multiplies each row block as soon as it is
+// split; every block's weights are read from LDS while the block before is multiplied.
+template <int MB, int NB, bool ABS>
+__device__ __forceinline__ void split_step(const float *as, int ch0, int ch1, const bf16x8 *ws, int nj,
+                                           uint32_t abs_mask, f32v4 (&hi)[MB][NB], f32v4 (&lo)[MB][NB]) {
+  auto load_w = [&](int j) {
+    const Split8 w{ws[j * 192], ws[j * 192 + 64], ws[j * 192 + 128]};
+    return ABS ? split_abs(w, abs_mask) : w;
+  };
+  f32v4 x[MB], y[MB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i) {
+    x[i] = *reinterpret_cast<const f32v4 *>(as + i * 512 + ch0);
+    y[i] = *reinterpret_cast<const f32v4 *>(as + i * 512 + ch1);
+  }
+  Split8 a[MB], w[2];
+  w[0] = load_w(0);
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    if (j < nj) {
+      if (j + 1 < NB) w[(j + 1) & 1] = load_w(j + 1);
+      if (j == 0) {
+#pragma unroll
+        for (int i = 0; i < MB; ++i) {
+          a[i] = split8(x[i], y[i]);
+          split_mma1(a[i], w[0], hi[i][0], lo[i][0]);
+        }
+      } else {
+        split_mma<MB, NB>(a, w[j & 1], hi, lo, j);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+}
+
 }  // namespace vcr
