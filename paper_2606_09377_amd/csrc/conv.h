@@ -139,6 +139,7 @@ struct FwdConvArgs {
   int64_t in_rs;
   int32_t Ci, Hi;
   const float *Wk;         // [Co][3][3][Ci]
+  const uint16_t *Ws;      // Wk split into bf16 parts (split_bf16.h), or null: float32 products
   const float *bias;       // [Co]
   int32_t Co, Ho, stride;
   int32_t rows;

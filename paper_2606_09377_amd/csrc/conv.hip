@@ -470,6 +470,10 @@ __global__ __launch_bounds__(256, MINB) void k_convt(const ConvTArgs p) {
   convt_epilogue<BM, BN, WM, WN, RELU, AL, SPL>(p, cl, tab, acc, m0, n0, nt, &As[0][0]);
 }
 
+// row offsets of coefficient row r at output position pos (gradient pass; below)
+__device__ __forceinline__ void fwd_offsets(const FwdConvArgs &p, int64_t r, int32_t pos, int64_t *ob, int64_t *pb,
+                                            int64_t *rb);
+
 }  // namespace vcr
 
 #include "conv_split.h"
@@ -1664,6 +1668,8 @@ hipError_t launch_fwd_conv(const FwdConvArgs &a, hipStream_t s) {
   const int64_t M = (int64_t)a.rows * HW;
   if (M >= ((int64_t)1 << 31)) return hipErrorInvalidValue;
   const FastDiv dp = make_fastdiv((uint32_t)HW);
+  if (a.Ws && a.Ci % 32 == 0 && a.Co % 16 == 0 && a.out_rs % 4 == 0 && (!a.res || a.res_rs % 4 == 0))
+    return launch_fwd_conv_split(a, dp, s);
   if (a.Co % 128 == 0) {
     const int64_t blk = (M + 127) / 128 * (a.Co / 128);
     hipLaunchKernelGGL((k_fwd_conv<128, 128, 2, 2>), dim3((unsigned)blk), dim3(256), 0, s, a, dp);

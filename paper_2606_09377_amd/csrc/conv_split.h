@@ -313,4 +313,163 @@ static hipError_t launch_convt_split(const ConvTArgs &a, int64_t blk, hipStream_
   return hipGetLastError();
 }
 
+// Forward convolution of the gradient pass (k_fwd_conv) on the same tiles: the epilogue's row
+// offsets are computed once per workgroup under the first K step.
+struct FwdRows {
+  int64_t ob[CS_BM], pb[CS_BM], rb[CS_BM];   // ob -1: past the last row
+  int r[CS_BM];
+};
+
+template <int WN>
+__global__ __launch_bounds__(ConvSplit<WN>::T, 3) void k_fwd_conv_split(const FwdConvArgs p, FastDiv div_pos) {
+  typedef ConvSplit<WN> CS;
+  constexpr int MB = CS::MB, NB = CS::NB;
+  __shared__ __attribute__((aligned(16))) float lds[2 * (CS::A_FLOATS + CS::B_FLOATS)];
+  __shared__ FwdRows rows;
+  float *As = lds, *Bs = lds + 2 * CS::A_FLOATS;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave % CS::WM, wn = wave / CS::WM;
+  const int n_nt = (p.Co + CS::BN - 1) / CS::BN;
+  const int mt = blockIdx.x / n_nt, nt = blockIdx.x - mt * n_nt;
+  const int64_t m0 = (int64_t)mt * CS_BM;
+  const int n0 = nt * CS::BN;
+  const int HW = p.Ho * p.Ho;
+  const int64_t Mtot = (int64_t)p.rows * HW;
+  const int nj = min(max((p.Co - (n0 + wn * 64) + 15) / 16, 0), NB);   // column blocks with real channels
+
+  // per load of this wave: 8 output positions, 8 chunks of 16 bytes each; the source address
+  // under tap (0, 0) and a bit per tap row and column that lies inside the image
+  const float *a_row[CS::AQ];
+  uint32_t ty_ok[CS::AQ], tx_ok[CS::AQ];
+#pragma unroll
+  for (int q = 0; q < CS::AQ; ++q) {
+    const int row = (q * CS::NW + wave) * 8 + (lane >> 3);
+    const bool valid = m0 + row < Mtot;
+    const uint32_t m = valid ? (uint32_t)(m0 + row) : 0u;
+    const uint32_t r = fdiv(m, div_pos);
+    const int pos = (int)(m - r * (uint32_t)HW);
+    const int yo = pos / p.Ho, xo = pos - yo * p.Ho;
+    const int y0 = yo * p.stride - 1, x0 = xo * p.stride - 1;
+    a_row[q] = p.in + (int64_t)r * p.in_rs + ((int64_t)y0 * p.Hi + x0) * p.Ci + ((lane & 7) ^ lds_swz<32>(row)) * 4;
+    ty_ok[q] = tx_ok[q] = 0;
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      ty_ok[q] |= (uint32_t)(valid && (unsigned)(y0 + t) < (unsigned)p.Hi) << t;
+      tx_ok[q] |= (uint32_t)((unsigned)(x0 + t) < (unsigned)p.Hi) << t;
+    }
+  }
+  const int cpt = p.Ci / 32;
+  int l_ty = 0, l_tx = 0, l_cb = 0;   // the next step to load: channel blocks outer, taps inner
+  auto gload = [&](int buf) {
+    const int64_t off = ((int64_t)l_ty * p.Hi + l_tx) * p.Ci + l_cb * 32;
+#pragma unroll
+    for (int q = 0; q < CS::AQ; ++q) {
+      const float *src = (ty_ok[q] >> l_ty) & (tx_ok[q] >> l_tx) & 1 ? a_row[q] + off : g_zero4;
+      dma16(src, As + buf * CS::A_FLOATS + (q * CS::NW + wave) * 256);
+    }
+    const int kb = (3 * l_ty + l_tx) * cpt + l_cb;
+#pragma unroll
+    for (int q = 0; q < CS::BQ; ++q) {
+      const int i = q * CS::NW + wave, nb = i / 3, part = i - 3 * nb;
+      // column blocks past Co repeat the last one (never stored)
+      dma16(p.Ws + ((int64_t)min(n0 / 16 + nb, p.Co / 16 - 1) * (9 * cpt) + kb) * SPLIT_BLOCK + part * 512,
+            (uint32_t)lane * 16, Bs + buf * CS::B_FLOATS + i * 256);
+    }
+    if (++l_tx == 3) {
+      l_tx = 0;
+      if (++l_ty == 3) {
+        l_ty = 0;
+        ++l_cb;
+      }
+    }
+  };
+
+  f32v4 hi[MB][NB], lo[MB][NB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) hi[i][j] = lo[i][j] = f32v4{0.f, 0.f, 0.f, 0.f};
+  const int KT = 9 * cpt;
+  const int r16 = lane & 15, g4 = lane >> 4, sw = lds_swz<32>(r16);
+  const int ch0 = ((2 * g4) ^ sw) * 4, ch1 = ((2 * g4 + 1) ^ sw) * 4;
+  gload(0);
+  if (tid < CS_BM) {   // read after the loop's barriers
+    rows.ob[tid] = -1;
+    if (m0 + tid < Mtot) {
+      const uint32_t m = (uint32_t)(m0 + tid), r = fdiv(m, div_pos);
+      fwd_offsets(p, r, (int)(m - r * (uint32_t)HW), &rows.ob[tid], &rows.pb[tid], &rows.rb[tid]);
+      rows.r[tid] = (int)r;
+    }
+  }
+  for (int kt = 0; kt < KT; ++kt) {
+    const int cur = kt & 1;
+    wait_vmcnt<0>();   // this wave's part of step kt has landed
+    barrier_only();    // every wave's has, and step kt - 1's stage is free
+    if (kt + 1 < KT) gload(cur ^ 1);
+    split_step<MB, NB, false>(As + cur * CS::A_FLOATS + (wm * 32 + r16) * 32, ch0, ch1,
+                              reinterpret_cast<const bf16x8 *>(Bs + cur * CS::B_FLOATS) + wn * NB * 192 + lane, nj, 0u,
+                              hi, lo);
+  }
+  // epilogue: bias, then a residual, or the ReLU line with the slope gradient (fwd_apply), four
+  // channels of a row at once
+  const float4 *__restrict__ Pp = p.P;
+  const float *__restrict__ resp = p.res;
+  const float *__restrict__ alp = p.alpha;
+  const float *__restrict__ prep = p.pre;
+  float *__restrict__ outp = p.out;
+  float *__restrict__ gradp = p.grad;
+#pragma unroll
+  for (int i = 0; i < MB; ++i) {
+    const int lr = wm * 32 + 16 * i + r16;
+    const int64_t ob = rows.ob[lr], pb = rows.pb[lr], rb = rows.rb[lr];
+    const int r = rows.r[lr];
+    if (ob < 0) continue;
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      if (j >= nj) continue;
+      const int n = n0 + wn * 64 + 16 * j + 4 * g4;
+      f32v4 D = hi[i][j] + lo[i][j] + *reinterpret_cast<const f32v4 *>(p.bias + n);
+      if (resp) D += *reinterpret_cast<const f32v4 *>(resp + rb + n);
+      if (Pp) {
+        float4 prm[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) prm[v] = Pp[pb + n + v];
+        int ent[4] = {-1, -1, -1, -1};
+        float sterm[4] = {0.f, 0.f, 0.f, 0.f};
+        if (p.splits.D > 0) {   // subdomains (unit 0 only: pb + n is the neuron's index)
+          split_override4(p.splits, r, p.relu_index, (int)(pb + n), prm, ent, sterm);
+#pragma unroll
+          for (int v = 0; v < 4; ++v)
+            if (ent[v] >= 0 && p.splits.grad_beta)
+              p.splits.grad_beta[(int64_t)r * p.splits.S + ent[v]] = sterm[v] * D[v];
+        }
+        const f32v4 al = *reinterpret_cast<const f32v4 *>(alp + ob + n);
+        const f32v4 an = *reinterpret_cast<const f32v4 *>(prep + ob + n);
+        f32v4 o, gr;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const bool unst = prm[v].z > 0.f;
+          const float lam = unst ? al[v] : prm[v].x;
+          o[v] = an[v] > 0.f ? lam * D[v] : fmaf(prm[v].y, D[v], an[v] < 0.f ? prm[v].z : 0.f);
+          gr[v] = (unst && an[v] > 0.f) ? an[v] * D[v] : 0.f;
+        }
+        *reinterpret_cast<f32v4 *>(outp + ob + n) = o;
+        *reinterpret_cast<f32v4 *>(gradp + ob + n) = gr;
+      } else {
+        *reinterpret_cast<f32v4 *>(outp + ob + n) = D;
+      }
+    }
+  }
+}
+
+static hipError_t launch_fwd_conv_split(const FwdConvArgs &a, FastDiv dp, hipStream_t s) {
+  const int64_t M = (int64_t)a.rows * a.Ho * a.Ho, mt = (M + CS_BM - 1) / CS_BM;
+  if (a.Co % 128 == 0)
+    hipLaunchKernelGGL(k_fwd_conv_split<2>, dim3((unsigned)(mt * (a.Co / 128))), dim3(ConvSplit<2>::T), 0, s, a, dp);
+  else
+    hipLaunchKernelGGL(k_fwd_conv_split<1>, dim3((unsigned)(mt * ((a.Co + 63) / 64))), dim3(ConvSplit<1>::T), 0, s, a, dp);
+  return hipGetLastError();
+}
+
 }  // namespace vcr

@@ -854,8 +854,10 @@ vcr_status graph_load(vcr_ctx *c, const vcr_node *nodes, int32_t n, const int32_
     std::vector<SplitItem> items;
     for (int i = 0; i + 1 < n; ++i) {   // the output node is no product's operand
       GNode &gn = g->nodes[i];
-      if (gn.op == VCR_CONV2D && gn.Ci % 32 == 0 && gn.C % 32 == 0)   // not the stem
+      if (gn.op == VCR_CONV2D && gn.Ci % 32 == 0 && gn.C % 32 == 0) {   // not the stem
         items.push_back({gn.Bt, 9 * (int64_t)gn.C, gn.Ci_pad, 9 * (int64_t)gn.C, &gn.Bs});
+        items.push_back({gn.Wk, 9 * (int64_t)gn.Ci, gn.C, 9 * (int64_t)gn.Ci, &gn.Ws});
+      }
       if (gn.op != VCR_DENSE) continue;
       items.push_back({gn.Bt, gn.ld_out, gn.ld_in, gn.ld_out, &gn.Bs});
       items.push_back({gn.hwc_in ? gn.Wh : gn.Wp, gn.ld_in, gn.ld_out, gn.ld_in, &gn.Ws});
@@ -1187,6 +1189,7 @@ vcr_status run_forward(vcr_ctx *c, GraphNet *g, GBufs &bf, int u0, int units, in
         a.Ci = nd.Ci;
         a.Hi = nd.Hi;
         a.Wk = nd.Wk;
+        a.Ws = nd.Ws;
         a.bias = nd.b;
         a.Co = nd.C;
         a.Ho = nd.H;
