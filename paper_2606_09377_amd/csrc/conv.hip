@@ -667,7 +667,7 @@ hipError_t launch_convt_part(const ConvTArgs &a0, int part, hipStream_t s) {
   if (a.Bs && a.S_in <= 256 && a.Ha <= 256) {    // split operands: whole cache lines of 32 channels
     if (a.row_stride_out % 4 || a.row_stride_in % 4 || a.res_row_stride % 4 || a.C_in % 16) return hipErrorInvalidValue;
     const bool wide = a.N_pad % 128 == 0;
-    const int64_t blk = convt_fill(a, cu, d, CS_BM, wide ? 128 : 64);
+    const int64_t blk = convt_fill(a, cu, d, wide ? ConvSplit<2>::BM : ConvSplit<1>::BM, wide ? 128 : 64);
     if (blk < 0) return hipErrorInvalidValue;
     return wide ? launch_convt_split<2>(a, blk, s) : launch_convt_split<1>(a, blk, s);
   }

@@ -3,26 +3,28 @@
 //
 // The same implicit GEMMs as k_convt and k_fwd_conv (rows, position classes, taps, epilogues),
 // with K steps of 32 channels of one tap: a step gathers 128 contiguous bytes of each of the
-// tile's 96 source positions (one cache line, where the 16-channel steps of the float32 kernels
-// read two halves) and the weights' three parts, straight into double-buffered LDS.  Three waves
-// of 32 x 64 share a 64-column tile (53 KB: three workgroups per compute unit), six a 128-column
-// one (77 KB: two).  The tile is that small for the sake of those workgroups: on the 3 x 32 x 32
-// ResNet a 128-row tile (two workgroups) spends 19 us in its K loop, at 233 TFLOP/s, and as much
-// before and after it, which only other workgroups' K loops can hide.
+// tile's source positions (one cache line, where the 16-channel steps of the float32 kernels
+// read two halves) and the weights' three parts, straight into double-buffered LDS.  Waves of
+// 32 x 64: three share a 96 x 64 tile (54 KB: three workgroups per compute unit), eight a 128 x
+// 128 one.  The 64-column tile is that small for the sake of those workgroups: on the 3 x 32 x
+// 32 ResNet a 128-row one (two workgroups) spends 19 us in its K loop, at 233 TFLOP/s, and as
+// much before and after it, which only other workgroups' K loops can hide.  The 128-column tile
+// has twice the K loop: 96 rows (two workgroups) took 255 us a dispatch there, 128 rows 207.
 #pragma once
 
 #include "split_bf16.h"
 
 namespace vcr {
 
-constexpr int CS_BM = 96;   // GEMM rows per workgroup
 template <int WN>
 struct ConvSplit {
-  static constexpr int WM = CS_BM / 32, NW = WM * WN, T = 64 * NW, BN = 64 * WN;
+  static constexpr int BM = WN == 1 ? 96 : 128;              // GEMM rows per workgroup
+  static constexpr int WM = BM / 32, NW = WM * WN, T = 64 * NW, BN = 64 * WN;
+  static constexpr int MINB = WN == 1 ? 3 : 2;               // waves per SIMD the registers are sized for
   static constexpr int MB = 2, NB = 4;                       // a wave: 32 rows x 64 columns
-  static constexpr int A_FLOATS = CS_BM * 32, B_FLOATS = BN / 16 * SPLIT_BLOCK / 2;
-  static constexpr int AQ = CS_BM / 8 / NW, BQ = 3 * (BN / 16) / NW;   // loads of a wave per K step
-  static_assert(CS_BM / 8 % NW == 0 && 3 * (BN / 16) % NW == 0, "loads spread evenly over the waves");
+  static constexpr int A_FLOATS = BM * 32, B_FLOATS = BN / 16 * SPLIT_BLOCK / 2;
+  static constexpr int AQ = BM / 8 / NW, BQ = 3 * (BN / 16) / NW;   // loads of a wave per K step
+  static_assert(BM / 8 % NW == 0 && 3 * (BN / 16) % NW == 0, "loads spread evenly over the waves");
 };
 
 // Four consecutive channels of one destination position: the split neurons of the row's domain
@@ -50,10 +52,11 @@ __device__ __forceinline__ void split_override4(const SplitTable &st, int row, i
 // What the epilogue needs of a tile row, computed once per workgroup while the first K step is
 // in flight: output and residual offsets (residual -1: none), parameter offset (-1 outside the
 // image), partial-sum index (-1 past the last row) and coefficient row.
+constexpr int CS_ROWS = 128;   // the largest tile
 struct ConvRows {
-  int64_t ob[CS_BM], rb[CS_BM];
-  int pb[CS_BM], mo[CS_BM], r[CS_BM];
-  uint32_t yx[CS_BM];   // iy, ix, anchor y, anchor x, a byte each
+  int64_t ob[CS_ROWS], rb[CS_ROWS];
+  int pb[CS_ROWS], mo[CS_ROWS], r[CS_ROWS];
+  uint32_t yx[CS_ROWS];   // iy, ix, anchor y, anchor x, a byte each
 };
 
 __device__ __forceinline__ void conv_row_info(const ConvTArgs &p, const ConvClass &cl, ConvRows &rows, int m0, int tr) {
@@ -168,7 +171,7 @@ __device__ __forceinline__ void convt_split_epilogue(const ConvTArgs &p, const f
 }
 
 template <int WN, bool RELU, bool AL, bool SPL>
-__global__ __launch_bounds__(ConvSplit<WN>::T, 3) void k_convt_split(const ConvTArgs p) {
+__global__ __launch_bounds__(ConvSplit<WN>::T, ConvSplit<WN>::MINB) void k_convt_split(const ConvTArgs p) {
   typedef ConvSplit<WN> CS;
   constexpr int MB = CS::MB, NB = CS::NB;
   __shared__ __attribute__((aligned(16))) float lds[2 * (CS::A_FLOATS + CS::B_FLOATS)];
@@ -186,7 +189,7 @@ __global__ __launch_bounds__(ConvSplit<WN>::T, 3) void k_convt_split(const ConvT
   const int n_nt = p.N_pad / CS::BN;
   const int lb = bid - cl.blk0;
   const int mt = lb / n_nt, nt = lb - mt * n_nt;
-  const int m0 = mt * CS_BM, n0 = nt * CS::BN;
+  const int m0 = mt * CS::BM, n0 = nt * CS::BN;
   const int sh = p.stride == 2 ? 1 : 0;
   const int nj = min(max((p.C_in - (n0 + wn * 64) + 15) / 16, 0), NB);   // column blocks with real channels
   if (cl.clip) {   // workgroup-uniform
@@ -196,7 +199,7 @@ __global__ __launch_bounds__(ConvSplit<WN>::T, 3) void k_convt_split(const ConvT
 
   // the tile's rows decoded once, a row per thread (the clipped decode is a chain of dependent
   // LDS reads)
-  if (tid < CS_BM) {
+  if (tid < CS::BM) {
     const uint32_t m = (uint32_t)(m0 + tid);
     uint32_t r = 0;
     int iy = 0, ix = 0, anc = 0;
@@ -278,7 +281,7 @@ __global__ __launch_bounds__(ConvSplit<WN>::T, 3) void k_convt_split(const ConvT
   const int r16 = lane & 15, g4 = lane >> 4, sw = lds_swz<32>(r16);
   const int ch0 = ((2 * g4) ^ sw) * 4, ch1 = ((2 * g4 + 1) ^ sw) * 4;
   gload(0);
-  if (tid < CS_BM) conv_row_info(p, cl, rows, m0, tid);   // read after the loop's barriers
+  if (tid < CS::BM) conv_row_info(p, cl, rows, m0, tid);   // read after the loop's barriers
   for (int kt = 0; kt < KT; ++kt) {
     const int cur = kt & 1;
     wait_vmcnt<0>();   // this wave's part of step kt has landed
@@ -316,12 +319,12 @@ static hipError_t launch_convt_split(const ConvTArgs &a, int64_t blk, hipStream_
 // Forward convolution of the gradient pass (k_fwd_conv) on the same tiles: the epilogue's row
 // offsets are computed once per workgroup under the first K step.
 struct FwdRows {
-  int64_t ob[CS_BM], pb[CS_BM], rb[CS_BM];   // ob -1: past the last row
-  int r[CS_BM];
+  int64_t ob[CS_ROWS], pb[CS_ROWS], rb[CS_ROWS];   // ob -1: past the last row
+  int r[CS_ROWS];
 };
 
 template <int WN>
-__global__ __launch_bounds__(ConvSplit<WN>::T, 3) void k_fwd_conv_split(const FwdConvArgs p, FastDiv div_pos) {
+__global__ __launch_bounds__(ConvSplit<WN>::T, ConvSplit<WN>::MINB) void k_fwd_conv_split(const FwdConvArgs p, FastDiv div_pos) {
   typedef ConvSplit<WN> CS;
   constexpr int MB = CS::MB, NB = CS::NB;
   __shared__ __attribute__((aligned(16))) float lds[2 * (CS::A_FLOATS + CS::B_FLOATS)];
@@ -332,7 +335,7 @@ __global__ __launch_bounds__(ConvSplit<WN>::T, 3) void k_fwd_conv_split(const Fw
   const int wm = wave % CS::WM, wn = wave / CS::WM;
   const int n_nt = (p.Co + CS::BN - 1) / CS::BN;
   const int mt = blockIdx.x / n_nt, nt = blockIdx.x - mt * n_nt;
-  const int64_t m0 = (int64_t)mt * CS_BM;
+  const int64_t m0 = (int64_t)mt * CS::BM;
   const int n0 = nt * CS::BN;
   const int HW = p.Ho * p.Ho;
   const int64_t Mtot = (int64_t)p.rows * HW;
@@ -394,7 +397,7 @@ __global__ __launch_bounds__(ConvSplit<WN>::T, 3) void k_fwd_conv_split(const Fw
   const int r16 = lane & 15, g4 = lane >> 4, sw = lds_swz<32>(r16);
   const int ch0 = ((2 * g4) ^ sw) * 4, ch1 = ((2 * g4 + 1) ^ sw) * 4;
   gload(0);
-  if (tid < CS_BM) {   // read after the loop's barriers
+  if (tid < CS::BM) {   // read after the loop's barriers
     rows.ob[tid] = -1;
     if (m0 + tid < Mtot) {
       const uint32_t m = (uint32_t)(m0 + tid), r = fdiv(m, div_pos);
@@ -464,7 +467,9 @@ __global__ __launch_bounds__(ConvSplit<WN>::T, 3) void k_fwd_conv_split(const Fw
 }
 
 static hipError_t launch_fwd_conv_split(const FwdConvArgs &a, FastDiv dp, hipStream_t s) {
-  const int64_t M = (int64_t)a.rows * a.Ho * a.Ho, mt = (M + CS_BM - 1) / CS_BM;
+  const int64_t M = (int64_t)a.rows * a.Ho * a.Ho;
+  const int BM = a.Co % 128 == 0 ? ConvSplit<2>::BM : ConvSplit<1>::BM;
+  const int64_t mt = (M + BM - 1) / BM;
   if (a.Co % 128 == 0)
     hipLaunchKernelGGL(k_fwd_conv_split<2>, dim3((unsigned)(mt * (a.Co / 128))), dim3(ConvSplit<2>::T), 0, s, a, dp);
   else

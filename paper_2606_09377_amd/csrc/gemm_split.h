@@ -18,9 +18,12 @@ namespace vcr {
 // The tile shapes, by launch size; every shape gives the same bits.
 //   SplitL  128 x 128, 4 waves of 64 x 64, two stages of 40 KB: two workgroups per compute unit
 //   SplitM  64 x 64, 4 waves of 16 x 64
-//   SplitS  32 x 64, 4 waves of 16 x 32
-template <int BM_, int BN_, int WM_, int WN_, int NS_, int MINB_>
+//   SplitS  32 x 64, 4 waves of 16 x 32, three stages: a long contraction on one or two
+//           workgroups per compute unit waits on nothing but its own chain (1024 x 1024 outputs over
+//           K = 65536: 1465 us with two stages and LDS reads in line, 1220 us)
+template <int BM_, int BN_, int WM_, int WN_, int NS_, int MINB_, bool PIPE_ = false>
 struct SplitTile {
+  static constexpr bool PIPE = PIPE_;
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, NS = NS_, MINB = MINB_;
   static constexpr int NW = WM * WN, T = 64 * NW;
   static constexpr int MB = BM / WM / 16, NB = BN / WN / 16;   // 16 x 16 blocks of a wave
@@ -29,7 +32,7 @@ struct SplitTile {
 };
 typedef SplitTile<128, 128, 2, 2, 2, 2> SplitL;
 typedef SplitTile<64, 64, 4, 1, 2, 2> SplitM;
-typedef SplitTile<32, 64, 2, 2, 2, 2> SplitS;
+typedef SplitTile<32, 64, 2, 2, 3, 2, true> SplitS;
 
 // Parameters of four consecutive columns for one coefficient row, with the row's split neuron
 // (if any) replaced.  flags: the tile's split table (four entries of the row's domain), or null
@@ -267,18 +270,58 @@ __global__ __launch_bounds__(TS::T, TS::MINB) void k_gemm_split(const GemmArgs p
 #pragma unroll
   for (int s = 0; s < NS - 1; ++s)
     if (s < KT) issue(s, s);
-  int cur = 0;
-  for (int kt = 0; kt < KT; ++kt) {
-    // this wave's part of step kt has landed (the next NS - 2 steps may be in flight)
-    if (NS >= 3 && kt + 1 < KT) wait_vmcnt<NS >= 3 ? LPT : 0>();
-    else wait_vmcnt<0>();
-    static_assert(NS <= 3, "the waits assume at most one later step in flight");
-    barrier_only();   // every wave's part of step kt is in LDS, and step kt - 1's stage is free
-    if (kt + NS - 1 < KT) issue(kt + NS - 1, cur + NS - 1 >= NS ? cur - 1 : cur + NS - 1);
-    const float *as = As + cur * TS::A_FLOATS + (wm * (TS::BM / TS::WM) + r16) * 32;
-    const bf16x8 *bs = reinterpret_cast<const bf16x8 *>(Bs + cur * TS::B_FLOATS) + wn * NB * 192 + lane;
-    split_step<MB, NB, AFF>(as, ch0, ch1, bs, nj, abs_mask, hi, lo);
-    cur = cur + 1 == NS ? 0 : cur + 1;
+  if constexpr (TS::PIPE) {
+    // A few waves alone on a compute unit: step kt + 1's operands are read from LDS while step kt
+    // is split and multiplied.  A step's operands are all in registers by the barrier, so the
+    // barrier that publishes step kt + 1 also frees step kt's stage for step kt + NS.  (Two
+    // register sets, the loop unrolled by two, so that no set is copied.)
+    const float *as = As + (wm * (TS::BM / TS::WM) + r16) * 32;
+    const bf16x8 *bs = reinterpret_cast<const bf16x8 *>(Bs) + wn * NB * 192 + lane;
+    auto read = [&](int buf, SplitRaw<MB, NB> &r) {
+      split_read<MB, NB, AFF>(r, as + buf * TS::A_FLOATS, ch0, ch1, bs + buf * (TS::B_FLOATS / 4), abs_mask);
+    };
+    auto landed = [&](int later) {   // with `later` steps requested after the one waited for
+      if (NS >= 4 && later >= 2) wait_vmcnt<(NS >= 4 ? 2 : 0) * LPT>();
+      else if (NS >= 3 && later >= 1) wait_vmcnt<(NS >= 3 ? 1 : 0) * LPT>();
+      else wait_vmcnt<0>();
+      barrier_only();
+    };
+    int cur = 0;   // step kt's stage
+    auto step = [&](int kt, const SplitRaw<MB, NB> &now, SplitRaw<MB, NB> &next) {
+      const int nxt = cur + 1 == NS ? 0 : cur + 1;
+      if (kt + 1 < KT) {
+        landed(min(NS - 2, KT - 2 - kt));
+        if (kt + NS < KT) issue(kt + NS, cur);
+        read(nxt, next);
+      }
+      split_mma_all<MB, NB>(now, hi, lo);
+      cur = nxt;
+    };
+    SplitRaw<MB, NB> r0, r1;
+    if (KT > 0) {
+      if (NS - 1 < KT) issue(NS - 1, NS - 1);
+      wait_vmcnt<0>();
+      barrier_only();
+      read(0, r0);
+    }
+    for (int kt = 0; kt < KT; kt += 2) {
+      step(kt, r0, r1);
+      if (kt + 1 < KT) step(kt + 1, r1, r0);
+    }
+  } else {
+    int cur = 0;
+    for (int kt = 0; kt < KT; ++kt) {
+      // this wave's part of step kt has landed (the next NS - 2 steps may be in flight)
+      if (NS >= 3 && kt + 1 < KT) wait_vmcnt<NS >= 3 ? LPT : 0>();
+      else wait_vmcnt<0>();
+      static_assert(TS::PIPE || NS <= 3, "the waits assume at most one later step in flight");
+      barrier_only();   // every wave's part of step kt is in LDS, and step kt - 1's stage is free
+      if (kt + NS - 1 < KT) issue(kt + NS - 1, cur + NS - 1 >= NS ? cur - 1 : cur + NS - 1);
+      const float *as = As + cur * TS::A_FLOATS + (wm * (TS::BM / TS::WM) + r16) * 32;
+      const bf16x8 *bs = reinterpret_cast<const bf16x8 *>(Bs + cur * TS::B_FLOATS) + wn * NB * 192 + lane;
+      split_step<MB, NB, AFF>(as, ch0, ch1, bs, nj, abs_mask, hi, lo);
+      cur = cur + 1 == NS ? 0 : cur + 1;
+    }
   }
 #pragma unroll
   for (int i = 0; i < MB; ++i)

@@ -154,4 +154,44 @@ __device__ __forceinline__ void split_step(const float *as, int ch0, int ch1, co
   }
 }
 
+// A K step's operands of a wave in registers, read whole from LDS (the layout of split_step)
+template <int MB, int NB>
+struct SplitRaw {
+  f32v4 x[MB], y[MB];
+  Split8 w[NB];
+};
+template <int MB, int NB, bool ABS>
+__device__ __forceinline__ void split_read(SplitRaw<MB, NB> &r, const float *as, int ch0, int ch1, const bf16x8 *ws,
+                                           uint32_t abs_mask) {
+#pragma unroll
+  for (int i = 0; i < MB; ++i) {
+    r.x[i] = *reinterpret_cast<const f32v4 *>(as + i * 512 + ch0);
+    r.y[i] = *reinterpret_cast<const f32v4 *>(as + i * 512 + ch1);
+  }
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    const Split8 w{ws[j * 192], ws[j * 192 + 64], ws[j * 192 + 128]};
+    r.w[j] = ABS ? split_abs(w, abs_mask) : w;
+  }
+}
+// its products, every accumulator's in split_mma's order
+template <int MB, int NB>
+__device__ __forceinline__ void split_mma_all(const SplitRaw<MB, NB> &r, f32v4 (&hi)[MB][NB], f32v4 (&lo)[MB][NB]) {
+  Split8 a[MB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i) a[i] = split8(r.x[i], r.y[i]);
+  auto each = [&](auto &&f) {
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j) f(a[i], r.w[j], hi[i][j], lo[i][j]);
+  };
+  each([](const Split8 &p, const Split8 &w, f32v4 &, f32v4 &l) { l = mfma_bf16(w.l, p.h, l); });
+  each([](const Split8 &p, const Split8 &w, f32v4 &h, f32v4 &) { h = mfma_bf16(w.h, p.h, h); });
+  each([](const Split8 &p, const Split8 &w, f32v4 &, f32v4 &l) { l = mfma_bf16(w.h, p.l, l); });
+  each([](const Split8 &p, const Split8 &w, f32v4 &, f32v4 &l) { l = mfma_bf16(w.m, p.m, l); });
+  each([](const Split8 &p, const Split8 &w, f32v4 &, f32v4 &l) { l = mfma_bf16(w.m, p.h, l); });
+  each([](const Split8 &p, const Split8 &w, f32v4 &, f32v4 &l) { l = mfma_bf16(w.h, p.m, l); });
+}
+
 }  // namespace vcr
