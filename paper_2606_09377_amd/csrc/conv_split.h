@@ -52,14 +52,17 @@ __device__ __forceinline__ void split_override4(const SplitTable &st, int row, i
 // What the epilogue needs of a tile row, computed once per workgroup while the first K step is
 // in flight: output and residual offsets (residual -1: none), parameter offset (-1 outside the
 // image), partial-sum index (-1 past the last row) and coefficient row.
-constexpr int CS_ROWS = 128;   // the largest tile
+// Sized for the tile: at 128 rows it takes the third workgroup of 96-row tiles off a compute
+// unit (3 x 32 x 32 ResNet, two inputs: 55.6 against 47.4 ms).
+template <int ROWS>
 struct ConvRows {
-  int64_t ob[CS_ROWS], rb[CS_ROWS];
-  int pb[CS_ROWS], mo[CS_ROWS], r[CS_ROWS];
-  uint32_t yx[CS_ROWS];   // iy, ix, anchor y, anchor x, a byte each
+  int64_t ob[ROWS], rb[ROWS];
+  int pb[ROWS], mo[ROWS], r[ROWS];
+  uint32_t yx[ROWS];   // iy, ix, anchor y, anchor x, a byte each
 };
 
-__device__ __forceinline__ void conv_row_info(const ConvTArgs &p, const ConvClass &cl, ConvRows &rows, int m0, int tr) {
+template <int ROWS>
+__device__ __forceinline__ void conv_row_info(const ConvTArgs &p, const ConvClass &cl, ConvRows<ROWS> &rows, int m0, int tr) {
   const bool valid = m0 + tr < cl.M;
   const int r = rows.r[tr];
   const uint32_t yx = rows.yx[tr];
@@ -83,7 +86,8 @@ __device__ __forceinline__ void conv_row_info(const ConvTArgs &p, const ConvClas
 // or residuals are loaded four blocks ahead: with one block ahead the eight blocks of a wave
 // were eight waits on the L2.
 template <int WN, bool RELU, bool AL, bool SPL>
-__device__ __forceinline__ void convt_split_epilogue(const ConvTArgs &p, const f32v4 (&acc)[2][4], const ConvRows &rows,
+__device__ __forceinline__ void convt_split_epilogue(const ConvTArgs &p, const f32v4 (&acc)[2][4],
+                                                     const ConvRows<ConvSplit<WN>::BM> &rows,
                                                      int n0, int nt, int wm, int wn, int nj) {
   typedef ConvSplit<WN> CS;
   constexpr int MB = CS::MB, NB = CS::NB;
@@ -176,7 +180,7 @@ __global__ __launch_bounds__(ConvSplit<WN>::T, ConvSplit<WN>::MINB) void k_convt
   constexpr int MB = CS::MB, NB = CS::NB;
   __shared__ __attribute__((aligned(16))) float lds[2 * (CS::A_FLOATS + CS::B_FLOATS)];
   __shared__ ClipTab tab;
-  __shared__ ConvRows rows;
+  __shared__ ConvRows<CS::BM> rows;
   float *As = lds, *Bs = lds + 2 * CS::A_FLOATS;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -318,9 +322,10 @@ static hipError_t launch_convt_split(const ConvTArgs &a, int64_t blk, hipStream_
 
 // Forward convolution of the gradient pass (k_fwd_conv) on the same tiles: the epilogue's row
 // offsets are computed once per workgroup under the first K step.
+template <int ROWS>
 struct FwdRows {
-  int64_t ob[CS_ROWS], pb[CS_ROWS], rb[CS_ROWS];   // ob -1: past the last row
-  int r[CS_ROWS];
+  int64_t ob[ROWS], pb[ROWS], rb[ROWS];   // ob -1: past the last row
+  int r[ROWS];
 };
 
 template <int WN>
@@ -328,7 +333,7 @@ __global__ __launch_bounds__(ConvSplit<WN>::T, ConvSplit<WN>::MINB) void k_fwd_c
   typedef ConvSplit<WN> CS;
   constexpr int MB = CS::MB, NB = CS::NB;
   __shared__ __attribute__((aligned(16))) float lds[2 * (CS::A_FLOATS + CS::B_FLOATS)];
-  __shared__ FwdRows rows;
+  __shared__ FwdRows<CS::BM> rows;
   float *As = lds, *Bs = lds + 2 * CS::A_FLOATS;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
