@@ -5,6 +5,7 @@
 // every row maximises its own lower bound.  The per-layer state arrays are [M_pad][ld] with
 // the GEMM's row and column padding.
 #include "kernels.h"
+#include "row_sums.h"
 
 namespace vcr {
 
@@ -66,14 +67,11 @@ hipError_t launch_alpha_vertex(const float *pre0, int64_t ld0, const float *c0, 
   return hipGetLastError();
 }
 
-__global__ void k_alpha_best(const float *beta, const float *cpart, int32_t n_parts, int32_t M_pad, int32_t rows,
-                             int32_t m, int32_t first, float *best_val, int32_t *flag, float *hist_lb,
+__global__ void k_alpha_best(const RowConst rc, int32_t rows, int32_t m, int32_t first, float *best_val, int32_t *flag, float *hist_lb,
                              float *hist_ub) {
   const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (row >= rows) return;
-  float sp = 0.f;
-  for (int p = 0; p < n_parts; ++p) sp += cpart[(int64_t)p * M_pad + row];
-  const float v = beta[row] + sp;
+  const float v = row_const(rc, row);
   const bool better = first || v > best_val[row];
   if (better) best_val[row] = v;
   flag[row] = better ? 1 : 0;
@@ -87,11 +85,9 @@ __global__ void k_alpha_best(const float *beta, const float *cpart, int32_t n_pa
   }
 }
 
-hipError_t launch_alpha_best(const float *beta, const float *cpart, int32_t n_parts, int32_t M_pad, int32_t rows,
-                             int32_t m, int32_t first, float *best_val, int32_t *flag, float *hist_lb,
+hipError_t launch_alpha_best(const RowConst &rc, int32_t rows, int32_t m, int32_t first, float *best_val, int32_t *flag, float *hist_lb,
                              float *hist_ub, hipStream_t s) {
-  hipLaunchKernelGGL(k_alpha_best, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, s, beta, cpart, n_parts, M_pad,
-                     rows, m, first, best_val, flag, hist_lb, hist_ub);
+  hipLaunchKernelGGL(k_alpha_best, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, s, rc, rows, m, first, best_val, flag, hist_lb, hist_ub);
   return hipGetLastError();
 }
 

@@ -736,12 +736,14 @@ size_t carve_bytes(const vcr_ctx *c, const Plan &p, int32_t S) {
 
 // One backward pass through layers j = top .. 1 for `units` units of rows_per_unit rows
 // that start in A[0] (already relaxed for ReLU top-1... i.e. coefficients on z_top).
-// Leaves beta with the constants and cpart with the concretization partials.
+// Leaves the rows' constants in *rc: beta (the first rows'), the relaxing steps' sums in part,
+// each step adding to the slabs of the steps before, and the concretization's in cpart.
 vcr_status run_chain(vcr_ctx *c, CallBufs &bf, int top, int32_t M, int32_t rows_per_unit, int32_t units,
                      int32_t unit0, int32_t param_per_unit, const SplitTable &st, uint64_t *flops,
-                     bool with_alpha = false) {
+                     RowConst *rc, bool with_alpha = false) {
   const int32_t M_pad = (int32_t)rows_pad(M);
   int cur = 0;
+  int32_t slabs = 0;
   for (int j = top; j >= 1; --j) {
     const DenseLayer &W = c->layers[j - 1];   // layer j: z_j = W_j h_{j-1} + b_j
     GemmArgs g{};
@@ -769,6 +771,8 @@ vcr_status run_chain(vcr_ctx *c, CallBufs &bf, int top, int32_t M, int32_t rows_
       g.ldp = W.ld_in;
       g.relu_index = r;
       g.part = bf.part;
+      g.part_slabs = slabs;
+      slabs = std::max(slabs, (int32_t)(W.ld_in / PART_COLS));
       if (with_alpha) {
         g.alpha = bf.al[r].alpha;
         g.ld_alpha = bf.al[r].ld;
@@ -792,11 +796,9 @@ vcr_status run_chain(vcr_ctx *c, CallBufs &bf, int top, int32_t M, int32_t rows_
       if (st != VCR_OK) return st;
     }
     *flops += gf;
-    if (j >= 2) {
-      HIP_TRY(c, launch_rowsum(bf.beta, bf.part, (int32_t)(W.ld_in / PART_COLS), M_pad, M, c->stream));
-      cur ^= 1;
-    }
+    if (j >= 2) cur ^= 1;
   }
+  *rc = RowConst{bf.beta, bf.part, bf.cpart, slabs, (int32_t)(ld_of(c->n0) / PART_COLS), M_pad};
   return VCR_OK;
 }
 
@@ -873,10 +875,10 @@ vcr_status alpha_spec(vcr_ctx *c, CallBufs &bf, const Plan &p, const AlphaCall &
       ia.ld_alpha = al[R - 1].ld;
       ia.pre = al[R - 1].pre;
       HIP_TRY(c, launch_init_rows(ia, s));
-      vcr_status st = run_chain(c, bf, L - 1, M, rpu, uc, dom ? 0 : u0, dom ? 0 : 1, tab, flops, true);
+      RowConst rc{};
+      vcr_status st = run_chain(c, bf, L - 1, M, rpu, uc, dom ? 0 : u0, dom ? 0 : 1, tab, flops, &rc, true);
       if (st != VCR_OK) return st;
-      HIP_TRY(c, launch_alpha_best(bf.beta, bf.cpart, (int32_t)(ld0 / PART_COLS), M_pad, M, m, t == 0, bf.best_val,
-                                   bf.flag, o.lb_hist ? o.lb_hist + ((int64_t)t * units + u0) * m : nullptr,
+      HIP_TRY(c, launch_alpha_best(rc, M, m, t == 0, bf.best_val, bf.flag, o.lb_hist ? o.lb_hist + ((int64_t)t * units + u0) * m : nullptr,
                                    o.ub_hist ? o.ub_hist + ((int64_t)t * units + u0) * m : nullptr, s));
       const bool step = t < o.iters;
       // rows that improved keep their slopes: here after the last evaluation, otherwise inside
@@ -1033,9 +1035,10 @@ vcr_status crown_impl(vcr_ctx *c, const float *x0, int32_t B, float eps, const f
       ia.out = bf.A[0];
       ia.beta = bf.beta;
       HIP_TRY(c, launch_init_rows(ia, s));
-      st = run_chain(c, bf, k - 1, M, 2 * n, bc, b0, 1, SplitTable{}, &flops);
+      RowConst rc{};
+      st = run_chain(c, bf, k - 1, M, 2 * n, bc, b0, 1, SplitTable{}, &flops, &rc);
       if (st != VCR_OK) return st;
-      HIP_TRY(c, launch_finalize_layer(bf.beta, bf.cpart, (int32_t)(ld0 / PART_COLS), (int32_t)rows_pad(M), bc, n,
+      HIP_TRY(c, launch_finalize_layer(rc, bc, n,
                                        bf.ibp_c[k - 1] + (int64_t)b0 * Wk.ld_out,
                                        bf.ibp_r[k - 1] + (int64_t)b0 * Wk.ld_out, Wk.ld_out, c->intersect, Wk.b,
                                        bf.Lb[k - 1] + (int64_t)b0 * n, bf.Ub[k - 1] + (int64_t)b0 * n,
@@ -1135,9 +1138,10 @@ vcr_status crown_impl(vcr_ctx *c, const float *x0, int32_t B, float eps, const f
       ia.out = bf.A[0];
       ia.beta = bf.beta;
       HIP_TRY(c, launch_init_rows(ia, s));
-      st = run_chain(c, bf, L - 1, M, 2 * m, uc, D > 0 ? 0 : u0, D > 0 ? 0 : 1, tab, &flops);
+      RowConst rc{};
+      st = run_chain(c, bf, L - 1, M, 2 * m, uc, D > 0 ? 0 : u0, D > 0 ? 0 : 1, tab, &flops, &rc);
       if (st != VCR_OK) return st;
-      HIP_TRY(c, launch_finalize_spec(bf.beta, bf.cpart, (int32_t)(ld0 / PART_COLS), (int32_t)rows_pad(M), uc, m,
+      HIP_TRY(c, launch_finalize_spec(rc, uc, m,
                                       D > 0 ? bf.flags + u0 : nullptr, lb + (int64_t)u0 * m,
                                       ub + (int64_t)u0 * m, s));
       ++chunks;

@@ -9,6 +9,7 @@
 // butterfly), so every bound is reproducible bit for bit and independent of batching.
 #include "kernels.h"
 #include "relax.h"
+#include "row_sums.h"
 #include "../../include/vcrown.h"
 
 namespace vcr {
@@ -436,27 +437,10 @@ hipError_t launch_init_rows(const InitArgs &a, hipStream_t s) {
 }
 
 // ------------------------------------------------------------------------------------
-// beta[row] += sum_p part[p][row], p ascending.
-__global__ void k_rowsum(float *beta, const float *part, int32_t n_parts, int32_t M_pad, int32_t M) {
-  const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (row >= M) return;
-  float s = 0.f;
-  for (int p = 0; p < n_parts; ++p) s += part[(int64_t)p * M_pad + row];
-  beta[row] += s;
-}
-
-hipError_t launch_rowsum(float *beta, const float *part, int32_t n_parts, int32_t M_pad, int32_t M,
-                         hipStream_t s) {
-  hipLaunchKernelGGL(k_rowsum, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, s, beta, part, n_parts, M_pad, M);
-  return hipGetLastError();
-}
-
-// ------------------------------------------------------------------------------------
 // Bounds of one ReLU layer's pre-activations from the finished backward pass: lower rows
 // (b, 0, i) give l, negated upper rows (b, 1, i) give -u; then intersection with IBP and
 // the relaxation for the passes above.
-__global__ void k_finalize_layer(const float *beta, const float *cpart, int32_t n_parts, int32_t M_pad,
-                                 int32_t B, int32_t n, const float *ibp_c, const float *ibp_r, int64_t ld_ibp,
+__global__ void k_finalize_layer(const RowConst rc, int32_t B, int32_t n, const float *ibp_c, const float *ibp_r, int64_t ld_ibp,
                                  int32_t intersect, const float *bias_next, float *L, float *U, float4 *P,
                                  int64_t ldp, int32_t rule) {
   // one thread per (input, column) of P, padding columns included (they get zeros)
@@ -468,13 +452,9 @@ __global__ void k_finalize_layer(const float *beta, const float *cpart, int32_t 
     return;
   }
   const int64_t ml = b * 2 * n + i, mu = ml + n;
-  float sl = 0.f, su = 0.f;
-  for (int p = 0; p < n_parts; ++p) {
-    sl += cpart[(int64_t)p * M_pad + ml];
-    su += cpart[(int64_t)p * M_pad + mu];
-  }
-  float l = beta[ml] + sl;
-  float u = -(beta[mu] + su);
+  float l, u;
+  row_const2(rc, ml, mu, &l, &u);
+  u = -u;
   if (intersect) {
     const float c = ibp_c[b * ld_ibp + i], r = ibp_r[b * ld_ibp + i];
     l = fmaxf(l, c - r);
@@ -485,14 +465,12 @@ __global__ void k_finalize_layer(const float *beta, const float *cpart, int32_t 
   P[idx] = relax_params(l, u, bias_next[i], rule);
 }
 
-hipError_t launch_finalize_layer(const float *beta, const float *cpart, int32_t n_parts, int32_t M_pad,
-                                 int32_t B, int32_t n, const float *ibp_c, const float *ibp_r,
+hipError_t launch_finalize_layer(const RowConst &rc, int32_t B, int32_t n, const float *ibp_c, const float *ibp_r,
                                  int64_t ld_ibp, int32_t intersect, const float *bias_next,
                                  float *L, float *U, float4 *P, int64_t ldp, int32_t lam_rule, hipStream_t s) {
   if (ldp < n) return hipErrorInvalidValue;
   const int64_t tot = (int64_t)B * ldp;
-  hipLaunchKernelGGL(k_finalize_layer, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, beta, cpart,
-                     n_parts, M_pad, B, n, ibp_c, ibp_r, ld_ibp, intersect, bias_next, L, U, P, ldp, lam_rule);
+  hipLaunchKernelGGL(k_finalize_layer, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, rc, B, n, ibp_c, ibp_r, ld_ibp, intersect, bias_next, L, U, P, ldp, lam_rule);
   return hipGetLastError();
 }
 
@@ -566,19 +544,14 @@ hipError_t launch_spec_direct(const float *CW, int64_t ld_cw, const float *Cb, i
 
 // Final bounds per spec row: lb = beta + sum of concretization partials of the lower row,
 // ub = -(same for the negated row).  Infeasible units give (+inf, -inf), invalid ones NaN.
-__global__ void k_finalize_spec(const float *beta, const float *cpart, int32_t n_parts, int32_t M_pad,
-                                int32_t units, int32_t m, const int32_t *flags, float *lb, float *ub) {
+__global__ void k_finalize_spec(const RowConst rc, int32_t units, int32_t m, const int32_t *flags, float *lb, float *ub) {
   const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (idx >= (int64_t)units * m) return;
   const int64_t u = idx / m, i = idx - u * m;
   const int64_t ml = u * 2 * m + i, mu = ml + m;
-  float sl = 0.f, su = 0.f;
-  for (int p = 0; p < n_parts; ++p) {
-    sl += cpart[(int64_t)p * M_pad + ml];
-    su += cpart[(int64_t)p * M_pad + mu];
-  }
-  float l = beta[ml] + sl;
-  float h = -(beta[mu] + su);
+  float l, h;
+  row_const2(rc, ml, mu, &l, &h);
+  h = -h;
   const int f = flags ? flags[u] : 0;
   if (f == 1) {
     l = __int_as_float(0x7f800000);
@@ -591,12 +564,10 @@ __global__ void k_finalize_spec(const float *beta, const float *cpart, int32_t n
   ub[idx] = h;
 }
 
-hipError_t launch_finalize_spec(const float *beta, const float *cpart, int32_t n_parts, int32_t M_pad,
-                                int32_t units, int32_t m, const int32_t *unit_flags, float *lb,
+hipError_t launch_finalize_spec(const RowConst &rc, int32_t units, int32_t m, const int32_t *unit_flags, float *lb,
                                 float *ub, hipStream_t s) {
   const int64_t tot = (int64_t)units * m;
-  hipLaunchKernelGGL(k_finalize_spec, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, beta, cpart,
-                     n_parts, M_pad, units, m, unit_flags, lb, ub);
+  hipLaunchKernelGGL(k_finalize_spec, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, rc, units, m, unit_flags, lb, ub);
   return hipGetLastError();
 }
 

@@ -298,11 +298,15 @@ __device__ __forceinline__ void gemm_epilogue_body(const GemmArgs &p, f32x16 (&a
   // fixed butterfly over the 32 lanes that share rows (as a reduce-scatter: lane 2 v ends
   // with row v's sum)
   float *dst = partp + (int64_t)(col0 / PART_COLS) * p.M_pad;
+  const bool add = p.mode == EPI_RELAX && col0 / PART_COLS < p.part_slabs;
   const int v = r32 >> 1;
 #pragma unroll
   for (int bi = 0; bi < MB; ++bi) {
     const float x = half_wave_row_sums(rp[bi], r32);
-    if ((r32 & 1) == 0) dst[m0 + wrow + bi * 32 + (v >> 2) * 8 + half * 4 + (v & 3)] = x;
+    if ((r32 & 1) == 0) {
+      float *d = dst + m0 + wrow + bi * 32 + (v >> 2) * 8 + half * 4 + (v & 3);
+      *d = add ? *d + x : x;
+    }
   }
 }
 

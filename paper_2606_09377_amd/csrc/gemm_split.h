@@ -20,7 +20,7 @@ namespace vcr {
 //   SplitM  64 x 64, 4 waves of 16 x 64
 //   SplitS  32 x 64, 4 waves of 16 x 32, three stages: a long contraction on one or two
 //           workgroups per compute unit waits on nothing but its own chain (1024 x 1024 outputs over
-//           K = 65536: 1465 us with two stages and LDS reads in line, 1220 us)
+//           K = 65536: 1465 us with two stages and LDS reads in line, 1277 us)
 template <int BM_, int BN_, int WM_, int WN_, int NS_, int MINB_, bool PIPE_ = false>
 struct SplitTile {
   static constexpr bool PIPE = PIPE_;
@@ -180,6 +180,11 @@ __device__ __forceinline__ void split_epilogue(const GemmArgs &p, f32v4 (&acc)[T
     }
   }
   if constexpr (FWD || AFF) return;
+  // slabs that hold the sums of an earlier step of this pass are added to
+  auto add_part = [&](int s, int row, float x) {
+    float *d = p.part + (int64_t)s * p.M_pad + row;
+    *d = p.mode == EPI_RELAX && s < p.part_slabs ? *d + x : x;
+  };
   if constexpr (WIDE) {
 #pragma unroll
     for (int i = 0; i < MB; ++i)
@@ -188,7 +193,7 @@ __device__ __forceinline__ void split_epilogue(const GemmArgs &p, f32v4 (&acc)[T
         float x = slab[i][s];
         x += __shfl_xor(x, 16);
         x += __shfl_xor(x, 32);
-        if (g4 == 0) p.part[(int64_t)(col0 / PART_COLS + s) * p.M_pad + m0 + wrow + 16 * i + r16] = x;
+        if (g4 == 0) add_part(col0 / PART_COLS + s, m0 + wrow + 16 * i + r16, x);
       }
   } else {
     static_assert(WIDE || TS::BN % PART_COLS == 0, "a workgroup holds whole slabs");
@@ -206,7 +211,7 @@ __device__ __forceinline__ void split_epilogue(const GemmArgs &p, f32v4 (&acc)[T
       x += b[3 * TS::BM * 4];
       x += __shfl_xor(x, 1);
       x += __shfl_xor(x, 2);
-      if ((q & 3) == 0) p.part[(int64_t)(n0 / PART_COLS + s) * p.M_pad + m0 + (q >> 2)] = x;
+      if ((q & 3) == 0) add_part(n0 / PART_COLS + s, m0 + (q >> 2), x);
     }
   }
 }

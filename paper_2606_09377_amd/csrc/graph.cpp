@@ -1331,7 +1331,7 @@ vcr_status alpha_spec_graph(vcr_ctx *c, GraphNet *g, GBufs &bf, const PassPlan &
     for (int32_t t = 0; t <= o.iters; ++t) {
       vcr_status st = run_pass(c, g, bf, pp, u0, units, m, flops, true, dom ? &tab : nullptr);
       if (st != VCR_OK) return st;
-      HIP_TRY(c, launch_alpha_best(bf.beta, nullptr, 0, M_pad, M, m, t == 0, bf.best_val, bf.flag,
+      HIP_TRY(c, launch_alpha_best(RowConst{bf.beta, nullptr, nullptr, 0, 0, M_pad}, M, m, t == 0, bf.best_val, bf.flag,
                                    o.lb_hist ? o.lb_hist + ((int64_t)t * units_total + u0) * m : nullptr,
                                    o.ub_hist ? o.ub_hist + ((int64_t)t * units_total + u0) * m : nullptr, s));
       const bool step = t < o.iters;
@@ -1546,7 +1546,7 @@ vcr_status graph_run(vcr_ctx *c, const float *x0, int32_t B, float eps, const fl
         st = run_pass(c, g, bf, pp, u0, units, m, &flops, false, splits ? &tab : nullptr);
         if (st != VCR_OK) return st;
         ++chunks;
-        HIP_TRY(c, launch_finalize_spec(bf.beta, nullptr, 0, 0, units, m, splits ? bf.flags + u0 : nullptr,
+        HIP_TRY(c, launch_finalize_spec(RowConst{bf.beta, nullptr, nullptr, 0, 0, 0}, units, m, splits ? bf.flags + u0 : nullptr,
                                         lb + (int64_t)u0 * m, ub + (int64_t)u0 * m, s));
       }
       continue;
@@ -1577,7 +1577,7 @@ vcr_status graph_run(vcr_ctx *c, const float *x0, int32_t B, float eps, const fl
                                         z.b, bf.L[ri] + (int64_t)u0 * z.numel, bf.U[ri] + (int64_t)u0 * z.numel,
                                         bf.P[ri] + (int64_t)u0 * z.numel, c->lambda_rule, s));
       } else {
-        HIP_TRY(c, launch_finalize_layer(bf.beta, nullptr, 0, 0, units, (int32_t)z.numel,
+        HIP_TRY(c, launch_finalize_layer(RowConst{bf.beta, nullptr, nullptr, 0, 0, 0}, units, (int32_t)z.numel,
                                          bf.ic[pp.start] + (int64_t)u0 * ldz, bf.ir[pp.start] + (int64_t)u0 * ldz,
                                          ldz, c->intersect, z.b, bf.L[ri] + (int64_t)u0 * z.numel,
                                          bf.U[ri] + (int64_t)u0 * z.numel, bf.P[ri] + (int64_t)u0 * ldz, ldz,

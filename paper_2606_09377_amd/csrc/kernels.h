@@ -60,6 +60,8 @@ struct GemmArgs {
   int32_t rows_per_unit;   // rows of one input (intermediate: 2 n_k; final: 2 m)
   int32_t n_units;         // number of inputs that own rows (clamp for padding rows)
   float *part;             // [N_pad / PART_COLS][M_pad] per-row partial sums (null: EPI_FORWARD)
+  int32_t part_slabs;      // EPI_RELAX: the first part_slabs slabs of part hold an earlier step's
+                           // sums, which this step's are added to; the others are written
   // alpha-CROWN (all optional):
   //   alpha [M_pad][ld_alpha]: per-row lower slope of the ReLU relaxed in the epilogue, used
   //   at its unstable neurons (t > 0) instead of lam;
@@ -125,9 +127,14 @@ struct InitArgs {
   float *pre;            // optional: receives the rows before relaxation [M_pad][ldo]
 };
 hipError_t launch_init_rows(const InitArgs &a, hipStream_t s);
-hipError_t launch_rowsum(float *beta, const float *part, int32_t n_parts, int32_t M_pad, int32_t M,
-                         hipStream_t s);
-hipError_t launch_finalize_layer(const float *beta, const float *cpart, int32_t n_parts, int32_t M_pad,
+// The constant of a row: beta, plus its sums in the first n_slabs of part (the relaxing steps)
+// and the n_parts of cpart (the concretization), both of pitch M_pad; either may be empty.
+struct RowConst {
+  const float *beta, *part, *cpart;
+  int32_t n_slabs, n_parts;
+  int64_t M_pad;
+};
+hipError_t launch_finalize_layer(const RowConst &rc,
                                  int32_t B, int32_t n, const float *ibp_c, const float *ibp_r,
                                  int64_t ld_ibp, int32_t intersect, const float *bias_next,
                                  float *L, float *U, float4 *P, int64_t ldp, int32_t lam_rule, hipStream_t s);
@@ -137,8 +144,7 @@ hipError_t launch_spec_cw(const float *C, int32_t B, int32_t m, int32_t n_out, c
 hipError_t launch_spec_direct(const float *CW, int64_t ld_cw, const float *Cb, int32_t B, int32_t m,
                               int32_t n_in, const float *c, const float *r, int64_t ld_in,
                               int32_t relu_in, float *lb, float *ub, hipStream_t s);
-hipError_t launch_finalize_spec(const float *beta, const float *cpart, int32_t n_parts, int32_t M_pad,
-                                int32_t units, int32_t m, const int32_t *unit_flags, float *lb,
+hipError_t launch_finalize_spec(const RowConst &rc, int32_t units, int32_t m, const int32_t *unit_flags, float *lb,
                                 float *ub, hipStream_t s);
 struct SplitPrepArgs {
   const int32_t *relu_id, *neuron;
@@ -188,10 +194,9 @@ hipError_t launch_alpha_init(const AlphaLayer &l, const float *alpha_init, int64
 // E0 = c - sign(pre0) r per row (the box vertex that attains the row's bound)
 hipError_t launch_alpha_vertex(const float *pre0, int64_t ld0, const float *c0, const float *r0, int32_t rows_pad,
                                int32_t rows_per_unit, int32_t units, float *E0, hipStream_t s);
-// row bound = beta + sum of the concretization partials (the order of the final reduction);
-// best/flag update, optional history [units][m] lb and ub of this evaluation
-hipError_t launch_alpha_best(const float *beta, const float *cpart, int32_t n_parts, int32_t M_pad, int32_t rows,
-                             int32_t m, int32_t first, float *best_val, int32_t *flag, float *hist_lb,
+// row bound = the row's constant (the order of the final reduction); best/flag update, optional
+// history [units][m] lb and ub of this evaluation
+hipError_t launch_alpha_best(const RowConst &rc, int32_t rows, int32_t m, int32_t first, float *best_val, int32_t *flag, float *hist_lb,
                              float *hist_ub, hipStream_t s);
 // best <- alpha where the row improved
 hipError_t launch_alpha_keep(const AlphaLayer &l, const int32_t *flag, int32_t rows, hipStream_t s);

@@ -4,7 +4,35 @@
 
 #include <hip/hip_runtime.h>
 
+#include "kernels.h"
+
 namespace vcr {
+
+// The constant of a row, or of two at once: the slabs of the relaxing steps in order, then the
+// concretization's, then added to beta (loads issued four ahead of the adds).
+__device__ __forceinline__ float row_const(const RowConst &rc, int64_t row) {
+  float s = 0.f;
+#pragma unroll 4
+  for (int p = 0; p < rc.n_slabs; ++p) s += rc.part[p * rc.M_pad + row];
+#pragma unroll 4
+  for (int p = 0; p < rc.n_parts; ++p) s += rc.cpart[p * rc.M_pad + row];
+  return rc.beta[row] + s;
+}
+__device__ __forceinline__ void row_const2(const RowConst &rc, int64_t a, int64_t b, float *va, float *vb) {
+  float sa = 0.f, sb = 0.f;
+#pragma unroll 4
+  for (int p = 0; p < rc.n_slabs; ++p) {
+    sa += rc.part[p * rc.M_pad + a];
+    sb += rc.part[p * rc.M_pad + b];
+  }
+#pragma unroll 4
+  for (int p = 0; p < rc.n_parts; ++p) {
+    sa += rc.cpart[p * rc.M_pad + a];
+    sb += rc.cpart[p * rc.M_pad + b];
+  }
+  *va = rc.beta[a] + sa;
+  *vb = rc.beta[b] + sb;
+}
 
 // A half-wave (32 lanes, one column each) holds the constant terms of 16 rows, one value per
 // row and lane (rp[v]).  Returns the sum over the 32 lanes of row (r32 >> 1) & 15.  This is

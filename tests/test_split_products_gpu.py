@@ -1,11 +1,15 @@
 """The products on split bf16 operands: every tile shape at widths around its edges against the
 oracle, the same bits from every shape, and the float32 kernels where the device has no room for
 the split weights."""
+import contextlib
+
 import numpy as np
 import pytest
 
-from tests.gpu_util import assert_close, check_input, gpu_crown, gpu_ctx
-from workloads import random_mlp
+from tests.gpu_util import assert_close, check_input, gpu_crown, gpu_ctx, to_dev
+from tests.test_alpha_gpu import _assert_grad_close
+from workloads import Workload, random_mlp
+from workloads.gen import margin_spec, resnet_net
 
 pytestmark = pytest.mark.gpu
 
@@ -19,6 +23,20 @@ def test_tile_edges(dims):
     wl = random_mlp(900 + dims[0], dims, 3, 0.02)
     lb, ub, layers = gpu_crown(gpu_ctx(wl.net), wl)
     for b in range(3):
+        check_input(wl.net, wl.x0[b], wl.eps, wl.C[b], lb[b], ub[b], [(l[b], u[b]) for l, u in layers], what=f"input {b}")
+
+
+# a chain's constant terms are summed per 64-column slab over its steps: slabs of one step that
+# the next has not, and the other way round (widths going up and down again), one input and many
+@pytest.mark.parametrize("dims", [[20, 700, 40, 260, 90, 3], [20, 30, 200, 500, 66, 64, 2]],
+                         ids=lambda d: "x".join(map(str, d)))
+def test_constants_over_changing_widths(dims):
+    wl = random_mlp(920 + len(dims), dims, 40, 0.02)
+    ctx = gpu_ctx(wl.net)
+    lb, ub, layers = gpu_crown(ctx, wl)
+    for b in (0, 39):
+        l1, u1, _ = gpu_crown(ctx, wl, inputs=[b])
+        assert np.array_equal(l1[0], lb[b]) and np.array_equal(u1[0], ub[b])
         check_input(wl.net, wl.x0[b], wl.eps, wl.C[b], lb[b], ub[b], [(l[b], u[b]) for l, u in layers], what=f"input {b}")
 
 
@@ -52,22 +70,68 @@ def test_large_and_small_magnitudes():
         assert np.array_equal(layers[1][1], ref_layers[1][1])
 
 
-def test_float32_kernels_when_memory_is_short():
-    """With less than an eighth of the device's memory left no split weights are kept; the bounds
-    come from the float32 kernels, within the parity tolerance."""
+@contextlib.contextmanager
+def short_memory():
+    """A sixteenth of the device's memory left free: less than split weights are kept with."""
     import torch
-    wl = random_mlp(951, [120, 200, 180, 9], 2, 0.03)
-    with_split = gpu_ctx(wl.net)
-    want = gpu_crown(with_split, wl)
     free, total = torch.cuda.mem_get_info()
     hold = torch.empty(max(free - total // 16, 1), dtype=torch.uint8, device="cuda")
     try:
-        ctx = gpu_ctx(wl.net)
-        assert ctx.stats()["net_bytes"] < with_split.stats()["net_bytes"]
-        lb, ub, layers = gpu_crown(ctx, wl)
+        yield
     finally:
         del hold
         torch.cuda.empty_cache()
+
+
+def test_float32_kernels_when_memory_is_short():
+    """The bounds then come from the float32 kernels, within the parity tolerance."""
+    wl = random_mlp(951, [120, 200, 180, 77, 300, 9], 2, 0.03)
+    with_split = gpu_ctx(wl.net)
+    want = gpu_crown(with_split, wl)
+    with short_memory():
+        ctx = gpu_ctx(wl.net)
+        assert ctx.stats()["net_bytes"] < with_split.stats()["net_bytes"]
+        lb, ub, layers = gpu_crown(ctx, wl)
     for b in range(2):
         check_input(wl.net, wl.x0[b], wl.eps, wl.C[b], lb[b], ub[b], [(l[b], u[b]) for l, u in layers])
         assert_close(lb[b], want[0][b].astype(np.float64), "float32 and split products")
+
+
+def odd_resnet(seed, hw, c1, c2, fc, n_out):
+    """resnet_net on an odd image side (its stride-2 maps round up, and so do the dense columns)."""
+    rng = np.random.default_rng(seed)
+    net = resnet_net(rng, in_chw=(3, hw, hw), c1=c1, c2=c2, fc=fc, n_out=n_out)
+    k = next(i for i, nd in enumerate(net.nodes) if nd.op == "flatten")
+    n_flat = c2 * ((hw + 1) // 2) ** 2
+    net.nodes[k + 1].W = (rng.standard_normal((fc, n_flat)) * np.sqrt(2 / n_flat)).astype(np.float32)
+    x0 = rng.random((2, net.n_in)).astype(np.float32)
+    return Workload(f"resnet{hw}", net, x0, np.float32(2 / 255), margin_spec(net, x0))
+
+
+# an odd image side (window positions and rows that fill no 96- or 128-row tile), the 64-column
+# blocks of 32 and 64 channels and the 128-column ones of 128, and stride 1 and 2
+@pytest.mark.parametrize("hw,c1,c2,fc", [(7, 32, 64, 33), (5, 64, 128, 20)])
+def test_convolutions_split_and_float32(hw, c1, c2, fc):
+    """Bounds, slope gradients of a convolutional network on split operands and, with memory
+    short, on the float32 kernels: each within the parity tolerance of the oracle, the gradients
+    of the two within the gradient's tolerance of each other."""
+    import torch
+    wl = odd_resnet(960 + hw, hw, c1, c2, fc, 5)
+    with_split = gpu_ctx(wl.net)
+
+    def run(ctx):
+        lb, ub, layers = gpu_crown(ctx, wl)
+        _, _, ex = ctx.alpha_crown_bounds(to_dev(wl.x0), wl.eps, to_dev(wl.C), iters=0, want_grad=True)
+        torch.cuda.synchronize()
+        return lb, ub, layers, ex["grad"].cpu().numpy()
+
+    a = run(with_split)
+    with short_memory():
+        ctx = gpu_ctx(wl.net)
+        assert ctx.stats()["net_bytes"] < with_split.stats()["net_bytes"]
+        f = run(ctx)
+    for lb, ub, layers, _ in (a, f):
+        for b in range(2):
+            check_input(wl.net, wl.x0[b], wl.eps, wl.C[b], lb[b], ub[b], [(l[b], u[b]) for l, u in layers])
+    _assert_grad_close(a[3], f[3].astype(np.float64), "gradients")
+    assert np.count_nonzero(f[3]) > 0
