@@ -159,7 +159,10 @@ typedef struct {
   uint64_t timed_conv_launches;
   double timed_conv_ms;
   uint64_t timed_conv_flops;
-  uint64_t net_bytes;               /* device memory holding the loaded network's weights */
+  /* device memory holding the loaded network's weights, the copies split into bf16 parts
+   * included while they are kept (6 bytes a weight and operand layout; left out where less than
+   * an eighth of the device's memory would stay free, dropped when a workspace needs the room) */
+  uint64_t net_bytes;
   /* the dense GEMM launches too small to fill the chip, which run a small-tile kernel (not
    * included in timed_gemm_*) */
   uint64_t timed_small_launches;

@@ -596,7 +596,7 @@ vcr_status check_finite_inputs(vcr_ctx *c, const float *x0, int32_t B, const flo
 }
 
 // IBP through dense layer W (c' = W c + b, r' = |W| r, after a ReLU on the input when
-// relu_in).  Large layers run as two fp32 MFMA GEMMs; the choice depends on the layer's size
+// relu_in).  Large layers run as two GEMMs on the matrix cores (launch_gemm); the choice depends on the layer's size
 // only, so an input's bounds do not depend on the batch it is in.  cin/rin and cout/rout
 // hold rows_pad(B) rows; tmp_c/tmp_r (same shape as cin) take the ReLU'd input.
 constexpr int64_t IBP_MFMA_MIN_WEIGHTS = (int64_t)1 << 24;

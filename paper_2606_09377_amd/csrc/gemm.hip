@@ -1,4 +1,4 @@
-// fp32 MFMA GEMM of the CROWN backward step (paper, Sec. 2.1, equation "crown"; the
+// GEMMs of the CROWN backward step (paper, Sec. 2.1, equation "crown"; the
 // per-layer step A <- A Lambda_i W_i of Sec. 3.3.2), with the next ReLU's relaxation and
 // the bias accumulation fused into the epilogue.
 //
@@ -8,7 +8,8 @@
 //   a   = (A' W_j)[row, n]                           coefficient on h_{j-1}, neuron n
 //   EPI_RELAX      : a'  = a > 0 ? lam a : s a       lower rule of ReLU j-1 at neuron n
 //                    out[row, n] = a'
-//                    part[row] += min(a, 0) t + a' b_{j-1}[n]
+//                    part[slab][row] += min(a, 0) t + a' b_{j-1}[n], slabs of 64 columns
+//                    (written, not added, where no earlier step of the pass has the slab)
 //                    (the relaxation intercept and the next linear layer's bias, i.e. the
 //                    constant terms this neuron adds to the bound)
 //   EPI_CONCRETIZE : part[row] += a c[n] - |a| r[n]  (j = 1: minimum of a . x over the box
@@ -24,9 +25,14 @@
 //
 // Upper bounds run through the same code on negated rows (max f = -min(-f)).
 //
-// Tiling for gfx950: 256 threads = 4 wave64 in a 2 x 2 grid, each wave owns a 64 x 64
+// The layers whose weights also lie split into bf16 parts run the kernels of gemm_split.h (784-1024x6
+// MLP, 64 inputs: 30.7 against 18.9 ms a call).  Those in this file multiply in float32 and run where
+// there is no such copy: the network was loaded with too little device memory left for it, the
+// copy was dropped to make room for a call's workspace, or rows are longer than 2^23.
+//
+// Tiling for gfx950 of the float32 kernels: 256 threads = 4 wave64 in a 2 x 2 grid, each wave owns a 64 x 64
 // block of the 128 x 128 tile as 2 x 2 v_mfma_f32_32x32x2f32 accumulators (64 fp32 each
-// lane).  K advances 32 at a time through double-buffered LDS (rows padded to 36 floats so
+// lane).  K advances 32 at a time through double-buffered LDS (16-byte chunks swizzled so
 // the 128-bit LDS reads of 8/16 consecutive lanes hit distinct banks).  Each lane consumes
 // 16 consecutive k of its operand rows per K tile, so every MFMA operand comes from one
 // 128-bit LDS read (the k order inside a tile is permuted identically for A and B, which
