@@ -197,6 +197,14 @@ vcr_status vcr_set_option(vcr_ctx *ctx, int32_t key, double value);
 #define VCR_MAX_NODE_ELEMENTS ((int64_t)1 << 30)
 #define VCR_MAX_LAYER_WEIGHTS ((int64_t)1 << 32)
 
+/* Arithmetic.  Everything is float32 in memory and in its sums.  The products of the dense and
+ * convolution steps multiply each float32 operand as three bf16 values, six of the nine partial
+ * products: a product is within 2^-24 of itself plus the rounding of its sum (a lone one within 1.65
+ * 2^-24, where a float32 multiply is within 2^-24; long sums come out closer to 64 bits than
+ * float32 multiply-adds).  Weights are taken exactly over float32's whole range, coefficients
+ * of a backward pass down to 2^-110; below that, each is rounded by up to 2^-134.  Results that
+ * overflow, or have infinite or NaN operands, are what float32 products give. */
+
 /* Load (copy) a network.  nodes[0..n) in topological order; the last node is the output and
  * must be VCR_DENSE.  in_chw is the input shape (C, H, W); for a flat input use
  * (n0, 1, 1).  Weight pointers are host memory and are not retained.  Replaces any

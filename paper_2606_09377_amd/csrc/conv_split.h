@@ -84,11 +84,12 @@ __device__ __forceinline__ void conv_row_info(const ConvTArgs &p, const ConvClas
 // Epilogue of the transposed convolution (see convt_epilogue): a lane holds, of GEMM rows
 // 16 i + lane % 16 of its wave, channels 16 j + 4 (lane / 16) .. + 3.  The relaxation parameters
 // or residuals are loaded four blocks ahead: with one block ahead the eight blocks of a wave
-// were eight waits on the L2.
-template <int WN, bool RELU, bool AL, bool SPL>
+// were eight waits on the L2.  finish() completes acc, up to the
+// factor it returns, under the first of those loads.
+template <int WN, bool RELU, bool AL, bool SPL, class Finish>
 __device__ __forceinline__ void convt_split_epilogue(const ConvTArgs &p, const f32v4 (&acc)[2][4],
                                                      const ConvRows<ConvSplit<WN>::BM> &rows,
-                                                     int n0, int nt, int wm, int wn, int nj) {
+                                                     int n0, int nt, int wm, int wn, int nj, Finish &&finish) {
   typedef ConvSplit<WN> CS;
   constexpr int MB = CS::MB, NB = CS::NB;
   const int lane = threadIdx.x & 63, r16 = lane & 15, g4 = lane >> 4;
@@ -115,6 +116,7 @@ __device__ __forceinline__ void convt_split_epilogue(const ConvTArgs &p, const f
 #pragma unroll
   for (int j = 0; j < NB; ++j)
     if (j < nj) fetch(0, j);
+  const float unscale = finish();
 #pragma unroll
   for (int i = 0; i < MB; ++i) {
     const int lr = lr0 + i * 16;
@@ -125,7 +127,9 @@ __device__ __forceinline__ void convt_split_epilogue(const ConvTArgs &p, const f
     for (int j = 0; j < NB; ++j) {
       if (j >= nj) continue;   // columns past C_in
       const int n = nw + j * 16;
-      const f32v4 a = acc[i][j] + rv[j];
+      f32v4 a;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) a[v] = fmaf(acc[i][j][v], unscale, rv[j][v]);
       float4 pr[4] = {prm[j][0], prm[j][1], prm[j][2], prm[j][3]};
       if (i + 1 < MB) fetch(i + 1, j);
       f32v4 o = {0.f, 0.f, 0.f, 0.f};
@@ -172,6 +176,23 @@ __device__ __forceinline__ void convt_split_epilogue(const ConvTArgs &p, const f
     x += __shfl_xor(x, 32);
     if (g4 == 0 && mo >= 0) p.part[(int64_t)(nt * WN + wn) * p.M_pad + mo] = x;
   }
+}
+
+// The source window of a tile row: its position under a zero shift, and the positions that lie
+// inside the window and, of a windowed source, inside the image
+struct ConvSource {
+  int iy, ix, ylo, yhi, xlo, xhi;
+};
+__device__ __forceinline__ ConvSource convt_source(const ConvTArgs &p, uint32_t yx) {
+  ConvSource s{(int)(yx & 255), (int)((yx >> 8) & 255), 0, p.S_out, 0, p.S_out};
+  if (p.src_scale > 0) {   // windowed source (Ha > 0)
+    const int oy = (int)((yx >> 16) & 255) * p.src_scale - p.src_h, ox = (int)(yx >> 24) * p.src_scale - p.src_h;
+    s.ylo = max(0, -oy);
+    s.xlo = max(0, -ox);
+    s.yhi = min(p.S_out, p.H_out - oy);
+    s.xhi = min(p.S_out, p.H_out - ox);
+  }
+  return s;
 }
 
 template <int WN, bool RELU, bool AL, bool SPL>
@@ -228,24 +249,15 @@ __global__ __launch_bounds__(ConvSplit<WN>::T, ConvSplit<WN>::MINB) void k_convt
 #pragma unroll
   for (int q = 0; q < CS::AQ; ++q) {
     const int row = (q * CS::NW + wave) * 8 + (lane >> 3);
-    const uint32_t yx = rows.yx[row];
-    const int iy = (int)(yx & 255), ix = (int)((yx >> 8) & 255);
-    int ylo = 0, xlo = 0, yhi = p.S_out, xhi = p.S_out;
-    if (p.src_scale > 0) {   // windowed source (Ha > 0)
-      const int oy = (int)((yx >> 16) & 255) * p.src_scale - p.src_h, ox = (int)(yx >> 24) * p.src_scale - p.src_h;
-      ylo = max(0, -oy);
-      xlo = max(0, -ox);
-      yhi = min(p.S_out, p.H_out - oy);
-      xhi = min(p.S_out, p.H_out - ox);
-    }
-    a_row[q] = p.A + (int64_t)rows.r[row] * p.row_stride_out + ((int64_t)iy * p.S_out + ix) * p.C_out +
+    const ConvSource src = convt_source(p, rows.yx[row]);
+    a_row[q] = p.A + (int64_t)rows.r[row] * p.row_stride_out + ((int64_t)src.iy * p.S_out + src.ix) * p.C_out +
                ((lane & 7) ^ lds_swz<32>(row)) * 4;
     ty_ok[q] = tx_ok[q] = 0;
 #pragma unroll
     for (int t = 0; t < 3; ++t) {
-      const int y = iy + shift_y(t), x = ix + shift_x(t);
-      ty_ok[q] |= (uint32_t)(y >= ylo && y < yhi) << t;
-      tx_ok[q] |= (uint32_t)(x >= xlo && x < xhi) << t;
+      const int y = src.iy + shift_y(t), x = src.ix + shift_x(t);
+      ty_ok[q] |= (uint32_t)(y >= src.ylo && y < src.yhi) << t;
+      tx_ok[q] |= (uint32_t)(x >= src.xlo && x < src.xhi) << t;
     }
     if (m0 + row >= cl.M) ty_ok[q] = 0;
   }
@@ -295,11 +307,26 @@ __global__ __launch_bounds__(ConvSplit<WN>::T, ConvSplit<WN>::MINB) void k_convt
                               reinterpret_cast<const bf16x8 *>(Bs + cur * CS::B_FLOATS) + wn * NB * 192 + lane, nj, 0u,
                               hi, lo);
   }
-#pragma unroll
-  for (int i = 0; i < MB; ++i)
-#pragma unroll
-    for (int j = 0; j < NB; ++j) hi[i][j] += lo[i][j];
-  convt_split_epilogue<WN, RELU, AL, SPL>(p, hi, rows, n0, nt, wm, wn, nj);
+  auto finish = [&] {
+    return split_finish<MB, NB>(
+        hi, lo, n0 + wn * 64, p.C_in, g4, [](int) { return true; },   // rows past the last are zeros
+        [&](int i, int j) {
+          const int row = wm * 32 + 16 * i + r16;
+          const ConvSource src = convt_source(p, rows.yx[row]);
+          const float *a = p.A + (int64_t)rows.r[row] * p.row_stride_out;
+          const float *w = p.Bt + (int64_t)(n0 + wn * 64 + 16 * j + r16) * p.ldb;
+          f32v4 x = {0.f, 0.f, 0.f, 0.f};
+          for (int ty = 0; ty < cl.nty; ++ty)
+            for (int tx = 0; tx < cl.ntx; ++tx) {
+              const int y = src.iy + shift_y(ty), xx = src.ix + shift_x(tx);
+              const bool ok = rows.mo[row] >= 0 && y >= src.ylo && y < src.yhi && xx >= src.xlo && xx < src.xhi;
+              x = mma_float32(ok ? a + ((int64_t)y * p.S_out + xx) * p.C_out : nullptr,
+                              w + (3 * (cl.ky0 + cl.kys * ty) + cl.kx0 + cl.kxs * tx) * p.C_out, p.C_out, g4, ~0u, x);
+            }
+          return x;
+        });
+  };
+  convt_split_epilogue<WN, RELU, AL, SPL>(p, hi, rows, n0, nt, wm, wn, nj, finish);
 }
 
 template <int WN>
@@ -419,6 +446,24 @@ __global__ __launch_bounds__(ConvSplit<WN>::T, ConvSplit<WN>::MINB) void k_fwd_c
                               reinterpret_cast<const bf16x8 *>(Bs + cur * CS::B_FLOATS) + wn * NB * 192 + lane, nj, 0u,
                               hi, lo);
   }
+  const float unscale = split_finish<MB, NB>(
+      hi, lo, n0 + wn * 64, p.Co, g4, [](int) { return true; },   // rows past the last are zeros
+      [&](int i, int j) {
+        const int row = wm * 32 + 16 * i + r16;
+        const bool valid = rows.ob[row] >= 0;
+        const uint32_t m = valid ? (uint32_t)(m0 + row) : 0u, r = fdiv(m, div_pos);
+        const int pos = (int)(m - r * (uint32_t)HW);
+        const int y0 = pos / p.Ho * p.stride - 1, x0 = pos % p.Ho * p.stride - 1;
+        const float *w = p.Wk + (int64_t)(n0 + wn * 64 + 16 * j + r16) * 9 * p.Ci;
+        f32v4 x = {0.f, 0.f, 0.f, 0.f};
+        for (int ty = 0; ty < 3; ++ty)
+          for (int tx = 0; tx < 3; ++tx) {
+            const bool ok = valid && (unsigned)(y0 + ty) < (unsigned)p.Hi && (unsigned)(x0 + tx) < (unsigned)p.Hi;
+            x = mma_float32(ok ? p.in + (int64_t)r * p.in_rs + ((int64_t)(y0 + ty) * p.Hi + x0 + tx) * p.Ci : nullptr,
+                            w + (3 * ty + tx) * p.Ci, p.Ci, g4, ~0u, x);
+          }
+        return x;
+      });
   // epilogue: bias, then a residual, or the ReLU line with the slope gradient (fwd_apply), four
   // channels of a row at once
   const float4 *__restrict__ Pp = p.P;
@@ -437,7 +482,9 @@ __global__ __launch_bounds__(ConvSplit<WN>::T, ConvSplit<WN>::MINB) void k_fwd_c
     for (int j = 0; j < NB; ++j) {
       if (j >= nj) continue;
       const int n = n0 + wn * 64 + 16 * j + 4 * g4;
-      f32v4 D = hi[i][j] + lo[i][j] + *reinterpret_cast<const f32v4 *>(p.bias + n);
+      f32v4 D = *reinterpret_cast<const f32v4 *>(p.bias + n);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) D[v] = fmaf(hi[i][j][v], unscale, D[v]);
       if (resp) D += *reinterpret_cast<const f32v4 *>(resp + rb + n);
       if (Pp) {
         float4 prm[4];

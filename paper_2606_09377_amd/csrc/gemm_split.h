@@ -328,10 +328,19 @@ __global__ __launch_bounds__(TS::T, TS::MINB) void k_gemm_split(const GemmArgs p
       cur = cur + 1 == NS ? 0 : cur + 1;
     }
   }
+  {
+    const int row0 = wm * (TS::BM / TS::WM) + r16, col0 = n0 + wn * (TS::BN / TS::WN);
+    const float unscale = split_finish<MB, NB>(
+        hi, lo, col0, p.N, g4, [&](int i) { return m0 + row0 + 16 * i < p.M; },
+        [&](int i, int j) {
+          return mma_float32(a_tile + (int64_t)(row0 + 16 * i) * p.lda, p.Bt + (int64_t)(col0 + 16 * j + r16) * p.ldb,
+                             p.K_real, g4, AFF && p.abs_b ? 0x7fffffffu : 0xffffffffu, f32v4{0.f, 0.f, 0.f, 0.f});
+        });
 #pragma unroll
-  for (int i = 0; i < MB; ++i)
+    for (int i = 0; i < MB; ++i)
 #pragma unroll
-    for (int j = 0; j < NB; ++j) hi[i][j] += lo[i][j];
+      for (int j = 0; j < NB; ++j) hi[i][j] *= unscale;
+  }
   __syncthreads();   // every wave is done with the operand buffers, which the epilogue reuses
   split_epilogue<TS, FWD, AL, AFF>(p, hi, m0, wm, wn, n0, lane, lds);
 }
@@ -345,7 +354,7 @@ __global__ void k_split_weights(const float *src, int64_t ld, int64_t N, int64_t
   const int64_t k = (t - row * per) * 8;
   const f32v4 x = *reinterpret_cast<const f32v4 *>(src + row * ld + k);
   const f32v4 y = *reinterpret_cast<const f32v4 *>(src + row * ld + k + 4);
-  const Split8 s = split8(x, y);
+  const Split8 s = split8(x * SPLIT_SCALE, y * SPLIT_SCALE);
   const int lane = (int)((k & 31) >> 3) * 16 + (int)(row & 15);
   bf16x8 *o = reinterpret_cast<bf16x8 *>(dst + ((row >> 4) * (K >> 5) + (k >> 5)) * SPLIT_BLOCK) + lane;
   o[0] = s.h;

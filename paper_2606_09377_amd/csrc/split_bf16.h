@@ -1,9 +1,26 @@
-// float32 products on the bf16 matrix cores: every float32 operand is the exact sum of three
-// bf16 values (8 significand bits each, 24 in all),
+// float32 products on the bf16 matrix cores: a float32 operand is the exact sum of three bf16
+// values (8 significand bits each, 24 in all),
 //   x = h + m + l,  h = bf16(x), m = bf16(x - h), l = x - h - m  (both differences are exact),
-// and a product takes the six of its nine partial products that reach 2^-24 of it,
-//   x y = h h' + (h l' + l h' + m m' + h m' + m h')
-// (the three left out are below 2^-25 together).  h h' and the five small ones are summed in two
+// and a product takes six of its nine partial products,
+//   x y = h h' + (h l' + l h' + m m' + h m' + m h').
+// The three left out, m l' + l m' + l l', are at most 2^-24 of the product together (|m| <= 2^-8,
+// |l| <= 2^-17 of the power of two below |x|; x = y = 0x3f807fc0 leaves out 2^-24.01).  A lone
+// product is so off by up to 1.65 2^-24 of itself, where a float32 multiply rounds by 2^-24 (rms
+// 2.59e-8 against 2.53e-8); sums gain what the accumulators below give.
+//
+// Range:
+// - Weights are split times 2^24 (SPLIT_SCALE), results multiplied back: every part is then a
+//   multiple of 2^-125 (float32's values are multiples of 2^-149), so the sum is exact for all of
+//   them, subnormal ones included.
+// - Coefficients are split as they are (scaling them too cost 3% of a large product, in the
+//   vector instructions of the split).  The sum is exact from 2^-110 on; below, what of a
+//   coefficient is less than 2^-133, the least bf16 value, is rounded: by up to 2^-134.
+// - Operands that round to infinity in bf16 (weights from 2^104, coefficients from 2^128 - 2^119),
+//   infinite or NaN ones and sums from 2^104 on leave results that are not finite.  Those are
+//   taken again in float32 from the float32 operands (split_finish), with the value, infinity
+//   or NaN that float32 gives.
+//
+// h h' and the five small ones are summed in two
 // accumulators, added once at the end.  In one accumulator the small partial products are
 // cut off at the large sum's precision, towards minus infinity: sums over K = 1024 normal
 // products came out 7.6e-8 of the result too low on average (3.3e-6 at K = 65536), and since a
@@ -29,6 +46,8 @@ namespace vcr {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32v4 __attribute__((ext_vector_type(4)));
+
+constexpr float SPLIT_SCALE = 0x1p24f, SPLIT_UNSCALE = 0x1p-24f;   // of a weight before its split, of a result
 
 // two values at once: the packed pairs of bf16 (element 0 in the low half)
 __device__ __forceinline__ void split_pair(float x0, float x1, uint32_t &h, uint32_t &m, uint32_t &l) {
@@ -192,6 +211,76 @@ __device__ __forceinline__ void split_mma_all(const SplitRaw<MB, NB> &r, f32v4 (
   each([](const Split8 &p, const Split8 &w, f32v4 &, f32v4 &l) { l = mfma_bf16(w.m, p.m, l); });
   each([](const Split8 &p, const Split8 &w, f32v4 &, f32v4 &l) { l = mfma_bf16(w.m, p.h, l); });
   each([](const Split8 &p, const Split8 &w, f32v4 &, f32v4 &l) { l = mfma_bf16(w.h, p.m, l); });
+}
+
+// ---- results out of the split range --------------------------------------------------------
+// 16 x 16 results in float32, the lane's four as mfma_bf16 leaves them: n contraction values
+// from the lane's two rows, a of coefficients and w of weights (|w| with mask 0x7fffffff), which
+// are 16-byte aligned and readable up to the next multiple of 16 values; a lane's null a is a row
+// of zeros.
+__device__ __forceinline__ f32v4 mma_float32(const float *a, const float *w, int n, int g4, uint32_t mask, f32v4 acc) {
+  for (int k = 4 * g4; k - 4 * g4 < n; k += 16) {   // as many rounds in every lane
+    const f32v4 y = *reinterpret_cast<const f32v4 *>(w + k);
+    f32v4 x = {0.f, 0.f, 0.f, 0.f};
+    if (a) x = *reinterpret_cast<const f32v4 *>(a + k);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float yq = y[q];   // (a bit cast of the vector's element itself takes element 0)
+      const float u = k + q < n ? x[q] : 0.f;
+      const float v = k + q < n ? __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, yq) & mask) : 0.f;
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(v, u, acc, 0, 0, 0);
+    }
+  }
+  return acc;
+}
+
+// A wave's results, hi + lo of every element, times a factor (returned, wave-uniform, left to the
+// caller's next multiply-add).  Elements that are not finite are replaced by their float32 values.
+// One multiply-add of two elements finds them (its sum is not finite then, nor where products
+// of elements overflow); the blocks that do hold one, in a row that counts (row_ok(i)), are taken
+// again one after the other, by again(i, j).  Columns from N on are padding, whose weights are zero,
+// and give zero.  The replacement is by element, so a result does not depend on its tile.
+template <int MB, int NB, class RowOk, class Again>
+__device__ __forceinline__ float split_finish(f32v4 (&v)[MB][NB], const f32v4 (&lo)[MB][NB], int col0, int N, int g4,
+                                              RowOk &&row_ok, Again &&again) {
+  auto finite = [](float x) { return fabsf(x) < __builtin_huge_valf(); };
+  bool bad = false;
+#pragma unroll
+  for (int i = 0; i < MB; ++i) {
+    float s = 0.f;
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      v[i][j] += lo[i][j];
+      s = fmaf(v[i][j][2], v[i][j][3], fmaf(v[i][j][0], v[i][j][1], s));
+    }
+    bad |= !finite(s) && row_ok(i);
+  }
+  if (__builtin_expect(!__any(bad), 1)) return SPLIT_UNSCALE;
+  uint32_t need = 0;   // a bit per block, wave-uniform
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j) {
+      const f32v4 q = v[i][j] *= SPLIT_UNSCALE;
+      const bool b = !(finite(q[0]) && finite(q[1]) && finite(q[2]) && finite(q[3])) && row_ok(i);
+      need |= (uint32_t)(__any(b) != 0) << (i * NB + j);
+    }
+#pragma unroll 1
+  while (need) {
+    const int b = __builtin_amdgcn_readfirstlane(__builtin_ctz(need));
+    need &= need - 1;
+    const f32v4 x = again(b / NB, b % NB);
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int j = 0; j < NB; ++j)
+        if (b == i * NB + j) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (!finite(v[i][j][q])) v[i][j][q] = col0 + 16 * j + 4 * g4 + q < N ? x[q] : 0.f;
+        }
+  }
+  return 1.f;
 }
 
 }  // namespace vcr

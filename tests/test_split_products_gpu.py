@@ -56,7 +56,7 @@ def test_every_tile_shape_gives_the_same_bits():
 
 def test_large_and_small_magnitudes():
     """Scaling a layer by 2^k and the next by 2^-k scales that layer's bounds by 2^k exactly and
-    leaves the others as they are, over most of float32's exponent range."""
+    leaves the others as they are (2^-60 and 2^50: the ends of the range have their own tests)."""
     base = random_mlp(941, [40, 70, 60, 7], 2, 0.05)
     ref_lb, ref_ub, ref_layers = gpu_crown(gpu_ctx(base.net), base)
     for k in (-60, 50):
