@@ -120,11 +120,13 @@ enum {
                                        synchronises the stream.  0 (default): no scan, and a
                                        non-finite input gives undefined bounds (Sec. 1.1 defines the
                                        input set for finite centres only). */
-  VCR_OPT_LAMBDA_RULE = 10          /* lower slope lambda of unstable ReLU neurons (Sec. 2.1 only
+  VCR_OPT_LAMBDA_RULE = 10,         /* lower slope lambda of unstable ReLU neurons (Sec. 2.1 only
                                        requires lambda in [0, 1], every value being sound):
                                        VCR_LAMBDA_ADAPTIVE (default), VCR_LAMBDA_ZERO, VCR_LAMBDA_ONE,
                                        VCR_LAMBDA_SAME_SLOPE.  Applies to every ReLU layer, to split
                                        neurons' relaxations and to alpha-CROWN's initial slopes. */
+  VCR_OPT_PRODUCTS = 11             /* how networks loaded from now on multiply (VCR_PRODUCTS_*; "Arithmetic"
+                                       below); the loaded one keeps the way it was loaded with */
 };
 
 /* Values of VCR_OPT_LAMBDA_RULE.  For an unstable neuron (l < 0 < u) with upper line slope
@@ -135,6 +137,13 @@ enum {
   VCR_LAMBDA_ZERO = 1,
   VCR_LAMBDA_ONE = 2,
   VCR_LAMBDA_SAME_SLOPE = 3
+};
+
+/* Values of VCR_OPT_PRODUCTS: SPLIT (default), on the bf16 matrix cores with operands split into
+ * bf16 values; FLOAT32, on the float32 matrix cores (about 1.6 times slower on large networks). */
+enum {
+  VCR_PRODUCTS_SPLIT = 0,
+  VCR_PRODUCTS_FLOAT32 = 1
 };
 
 typedef struct {
@@ -203,7 +212,8 @@ vcr_status vcr_set_option(vcr_ctx *ctx, int32_t key, double value);
  * 2^-24, where a float32 multiply is within 2^-24; long sums come out closer to 64 bits than
  * float32 multiply-adds).  Weights are taken exactly over float32's whole range, coefficients
  * of a backward pass down to 2^-110; below that, each is rounded by up to 2^-134.  Results that
- * overflow, or have infinite or NaN operands, are what float32 products give. */
+ * overflow, or have infinite or NaN operands, are what float32 products give.  VCR_OPT_PRODUCTS
+ * selects float32 multiply-adds instead. */
 
 /* Load (copy) a network.  nodes[0..n) in topological order; the last node is the output and
  * must be VCR_DENSE.  in_chw is the input shape (C, H, W); for a flat input use

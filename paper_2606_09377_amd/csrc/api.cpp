@@ -150,7 +150,7 @@ vcr_status ensure_ws(vcr_ctx *c, size_t bytes) {
 vcr_status split_operands(vcr_ctx *c, const std::vector<SplitItem> &items) {
   size_t bytes = 0, free_b = 0, total_b = 0;
   for (const SplitItem &it : items) bytes += al(sizeof(uint16_t) * 3 * (size_t)it.N * (size_t)it.K);
-  if (bytes == 0) return VCR_OK;
+  if (bytes == 0 || c->net_products == VCR_PRODUCTS_FLOAT32) return VCR_OK;
   HIP_TRY(c, hipMemGetInfo(&free_b, &total_b));
   if (bytes + total_b / 8 > free_b) return VCR_OK;
   void *base = nullptr;
@@ -385,6 +385,11 @@ vcr_status vcr_set_option(vcr_ctx *c, int32_t key, double v) {
         return fail(c, VCR_ERR_ARG, "lambda rule %g is not one of VCR_LAMBDA_*", v);
       c->lambda_rule = (int32_t)v;
       break;
+    case VCR_OPT_PRODUCTS:
+      if (v != VCR_PRODUCTS_SPLIT && v != VCR_PRODUCTS_FLOAT32)
+        return fail(c, VCR_ERR_ARG, "products %g is not one of VCR_PRODUCTS_*", v);
+      c->products = (int32_t)v;
+      break;
     case VCR_OPT_GRAPH:
       c->use_graph = v != 0.0;
       if (!c->use_graph && c->gexec) {
@@ -438,6 +443,7 @@ vcr_status vcr_load_net(vcr_ctx *c, const vcr_node *nodes, int32_t n, const int3
     }
     c->loaded = false;
     c->layers.clear();
+    c->net_products = c->products;
     st = graph_load(c, nodes, n, in_chw, sh);
     if (st != VCR_OK) return st;
     c->loaded = true;
@@ -450,6 +456,7 @@ vcr_status vcr_load_net(vcr_ctx *c, const vcr_node *nodes, int32_t n, const int3
   }
   destroy_graph(c->graph);
   c->graph = nullptr;
+  c->net_products = c->products;
   if (c->device < 0) {
     // validation-only context: remember the shapes for argument checks
     c->loaded = true;

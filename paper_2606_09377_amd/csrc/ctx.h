@@ -55,6 +55,7 @@ struct vcr_ctx {
   int32_t sync_check = 0;
   int32_t check_finite = 0;
   int32_t lambda_rule = 0;          // VCR_OPT_LAMBDA_RULE (relax.h)
+  int32_t products = 0;             // VCR_OPT_PRODUCTS, taken over by the next load
   // network
   bool loaded = false;
   int32_t n0 = 0;
@@ -70,6 +71,7 @@ struct vcr_ctx {
   void *split_base = nullptr;
   uint64_t split_bytes = 0;
   std::vector<uint16_t **> split_ptrs;
+  int32_t net_products = 0; // VCR_PRODUCTS_* of the loaded network
   uint64_t net_bytes = 0;   // device memory holding the loaded network (weights in their layouts)
   // last call
   int32_t last_B = 0;

@@ -273,3 +273,14 @@ def test_option_values_and_round_limit(vc):
     rid, neu, sg = _buf(4 * 65, np.int32), _buf(4 * 65, np.int32), _buf(4 * 65, np.int8)
     sp = vc.VcrSplits(4, vc.MAX_SPLITS + 1, rid.ctypes.data, neu.ctypes.data, sg.ctypes.data)
     assert _call(vc, ctx, 1, 0.1, 4, 20, 5, splits=sp) == vc.VCR_ERR_ARG
+
+
+def test_products_option_values(vc):
+    """VCR_OPT_PRODUCTS takes the VCR_PRODUCTS_* values only."""
+    ctx = vc.Ctx(-1)
+    for v in vc.PRODUCTS.values():
+        ctx.set_option(vc.OPT_PRODUCTS, v)
+    for v in (-1, len(vc.PRODUCTS), 0.5):
+        with pytest.raises(vc.VcrError) as e:
+            ctx.set_option(vc.OPT_PRODUCTS, v)
+        assert e.value.status == vc.VCR_ERR_ARG
