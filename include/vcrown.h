@@ -140,10 +140,14 @@ enum {
 };
 
 /* Values of VCR_OPT_PRODUCTS: SPLIT (default), on the bf16 matrix cores with operands split into
- * bf16 values; FLOAT32, on the float32 matrix cores (about 1.6 times slower on large networks). */
+ * bf16 values; FLOAT32, on the float32 matrix cores (about 1.6 times slower on large networks);
+ * SPLIT_NO_COPIES, SPLIT's bits without the split copies of dense weights (6 bytes a weight and
+ * operand layout, vcr_stats.net_bytes), about 1.2 times slower, 1.5 on single inputs: what SPLIT does by itself where the copies would
+ * leave less than an eighth of the device's memory free or a workspace needs their room. */
 enum {
   VCR_PRODUCTS_SPLIT = 0,
-  VCR_PRODUCTS_FLOAT32 = 1
+  VCR_PRODUCTS_FLOAT32 = 1,
+  VCR_PRODUCTS_SPLIT_NO_COPIES = 2
 };
 
 typedef struct {
@@ -169,8 +173,7 @@ typedef struct {
   double timed_conv_ms;
   uint64_t timed_conv_flops;
   /* device memory holding the loaded network's weights, the copies split into bf16 parts
-   * included while they are kept (6 bytes a weight and operand layout; left out where less than
-   * an eighth of the device's memory would stay free, dropped when a workspace needs the room) */
+   * included while they are kept (VCR_OPT_PRODUCTS) */
   uint64_t net_bytes;
   /* the dense GEMM launches too small to fill the chip, which run a small-tile kernel (not
    * included in timed_gemm_*) */

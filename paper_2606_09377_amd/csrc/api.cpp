@@ -150,7 +150,7 @@ vcr_status ensure_ws(vcr_ctx *c, size_t bytes) {
 vcr_status split_operands(vcr_ctx *c, const std::vector<SplitItem> &items) {
   size_t bytes = 0, free_b = 0, total_b = 0;
   for (const SplitItem &it : items) bytes += al(sizeof(uint16_t) * 3 * (size_t)it.N * (size_t)it.K);
-  if (bytes == 0 || c->net_products == VCR_PRODUCTS_FLOAT32) return VCR_OK;
+  if (bytes == 0 || c->net_products != VCR_PRODUCTS_SPLIT) return VCR_OK;
   HIP_TRY(c, hipMemGetInfo(&free_b, &total_b));
   if (bytes + total_b / 8 > free_b) return VCR_OK;
   void *base = nullptr;
@@ -386,7 +386,7 @@ vcr_status vcr_set_option(vcr_ctx *c, int32_t key, double v) {
       c->lambda_rule = (int32_t)v;
       break;
     case VCR_OPT_PRODUCTS:
-      if (v != VCR_PRODUCTS_SPLIT && v != VCR_PRODUCTS_FLOAT32)
+      if (v != VCR_PRODUCTS_SPLIT && v != VCR_PRODUCTS_FLOAT32 && v != VCR_PRODUCTS_SPLIT_NO_COPIES)
         return fail(c, VCR_ERR_ARG, "products %g is not one of VCR_PRODUCTS_*", v);
       c->products = (int32_t)v;
       break;
@@ -626,6 +626,7 @@ vcr_status ibp_layer(vcr_ctx *c, const DenseLayer &W, const float *cin, const fl
   g.lda = W.ld_in;
   g.Bt = W.Wp;
   g.Bs = W.Ws;
+  g.float32 = c->net_products == VCR_PRODUCTS_FLOAT32;
   g.ldb = W.ld_in;
   g.N = W.n_out;
   g.K_real = W.n_in;
@@ -758,6 +759,7 @@ vcr_status run_chain(vcr_ctx *c, CallBufs &bf, int top, int32_t M, int32_t rows_
     g.lda = W.ld_out;
     g.Bt = W.Bt;
     g.Bs = W.Bs;
+    g.float32 = c->net_products == VCR_PRODUCTS_FLOAT32;
     g.ldb = W.ld_out;
     g.N = W.n_in;
     g.K_real = W.n_out;
@@ -904,6 +906,7 @@ vcr_status alpha_spec(vcr_ctx *c, CallBufs &bf, const Plan &p, const AlphaCall &
         g.lda = W.ld_in;
         g.Bt = W.Wp;
         g.Bs = W.Ws;
+        g.float32 = c->net_products == VCR_PRODUCTS_FLOAT32;
         g.ldb = W.ld_in;
         g.N = W.n_out;
         g.K_real = W.n_in;

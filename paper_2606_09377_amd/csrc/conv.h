@@ -42,6 +42,7 @@ struct ConvTArgs {
   const float *Bt;         // [N_pad][ldb], ldb = 9 C_out: Bt[ci][(3 ky + kx) C_out + co]
   int64_t ldb;
   const uint16_t *Bs;      // Bt split into bf16 parts (split_bf16.h), or null: float32 products
+                           // (VCR_PRODUCTS_FLOAT32)
   int32_t N_pad;
   int32_t C_in, S_in, H_in;  // destination channels, window size, image size
   int64_t row_stride_in;     // S_in^2 C_in

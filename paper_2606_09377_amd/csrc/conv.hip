@@ -28,9 +28,9 @@
 //                                 identity (1, 1, 0, b[ci]) when the node is not a ReLU
 // and reduces the constants over the tile's columns into one partial per GEMM row.
 //
-// Convolutions whose weights also lie split into bf16 parts run the kernels of conv_split.h (3 x 32 x 32
-// ResNet, two inputs: 58.9 against 47.4 ms a call); k_convt and k_fwd_conv multiply in float32,
-// where there is no such copy (device memory short) or a window or map has sides above 256.
+// Convolutions run the kernels of conv_split.h (3 x 32 x 32 ResNet, two inputs: 58.9 against 47.4 ms a
+// call); k_convt and k_fwd_conv multiply in float32, for networks loaded with
+// VCR_PRODUCTS_FLOAT32 and, k_convt, where a window or map has sides above 256.
 #include "conv.h"
 #include "relax.h"
 #include "lds_dma.h"

@@ -1,5 +1,5 @@
 // The transposed convolution and the gradient pass's forward convolution on split operands
-// (split_bf16.h), run when the layer's split weights are present.  Part of conv.hip.
+// (split_bf16.h), run unless the network was loaded with float32 products.  Part of conv.hip.
 //
 // The same implicit GEMMs as k_convt and k_fwd_conv (rows, position classes, taps, epilogues),
 // with K steps of 32 channels of one tap: a step gathers 128 contiguous bytes of each of the

@@ -28,8 +28,8 @@ struct DenseLayer {
   float *Bt = nullptr;   // ld_in x ld_out, Bt[n][k] = W[k][n], zero padded
   float *b = nullptr;    // ld_out, zero padded
   // split copies (split_bf16.h) of Bt and Wp, the operands of the backward and of the forward
-  // and IBP products; null on the last layer (never a product's operand) and where the device
-  // has no room for them (split_operands)
+  // and IBP products; null on the last layer (never a product's operand) and where there are
+  // none (split_operands): the kernels then split Bt and Wp, with the same results
   uint16_t *Bs = nullptr, *Ws = nullptr;
 };
 
@@ -185,11 +185,10 @@ struct SplitItem {
   int64_t ld, N, K;
   uint16_t **dst;
 };
-// Splits the operands of a network being loaded.  The copies cost 6 bytes a weight beside the
-// float32 weights, which stay: where less than an eighth of the device's memory would remain
-// free beside them, or a later workspace needs the room (ensure_ws), there are none and the
-// products run on the float32 matrix instructions, so that what a device can load and bound
-// does not shrink.
+// Splits the operands of a network being loaded.  The copies cost 6 bytes a weight and layout
+// beside the float32 weights, which stay, and save time only (784-1024x6 MLP, 64 inputs: 18.6 against 21.8 ms):
+// there are none where the caller wants none, where less than an eighth of the device's memory
+// would remain free beside them, and once a workspace has needed the room (ensure_ws).
 vcr_status split_operands(vcr_ctx *c, const std::vector<SplitItem> &items);
 void drop_split_operands(vcr_ctx *c);
 

@@ -25,10 +25,9 @@
 //
 // Upper bounds run through the same code on negated rows (max f = -min(-f)).
 //
-// The layers whose weights also lie split into bf16 parts run the kernels of gemm_split.h (784-1024x6
-// MLP, 64 inputs: 30.7 against 18.9 ms a call).  Those in this file multiply in float32 and run where
-// there is no such copy: the network was loaded with too little device memory left for it, the
-// copy was dropped to make room for a call's workspace, or rows are longer than 2^23.
+// The steps run the kernels of gemm_split.h (784-1024x6 MLP, 64 inputs: 30.7 against 18.9 ms a call).
+// Those in this file multiply in float32 and run for networks loaded with VCR_PRODUCTS_FLOAT32 and
+// for rows longer than 2^23.
 //
 // Tiling for gfx950 of the float32 kernels: 256 threads = 4 wave64 in a 2 x 2 grid, each wave owns a 64 x 64
 // block of the 128 x 128 tile as 2 x 2 v_mfma_f32_32x32x2f32 accumulators (64 fp32 each
@@ -39,6 +38,8 @@
 // leaves the contraction unchanged).  Partial sums per row are reduced over the 32 columns
 // a lane group holds with a fixed butterfly, so results are deterministic and do not depend
 // on which other rows share the tile.
+#include <algorithm>
+
 #include "kernels.h"
 #include "lds_dma.h"
 #include "row_sums.h"
@@ -637,7 +638,8 @@ hipError_t launch_gemm(const GemmArgs &a, hipStream_t s) {
   if (a.mode != EPI_RELAX && a.mode != EPI_CONCRETIZE && a.mode != EPI_FORWARD && a.mode != EPI_AFFINE)
     return hipErrorInvalidValue;
   if (use_split(a)) {
-    if (a.M <= 0 || a.M > a.M_pad || a.N <= 0 || a.N > a.N_pad || a.K_real <= 0 || a.K_real > a.K || a.lda % 4 || ld % 4)
+    if (a.M <= 0 || a.M > a.M_pad || a.N <= 0 || a.N > a.N_pad || a.K_real <= 0 || a.K_real > a.K || a.lda % 4 || a.ldb % 4 ||
+        ld % 4)
       return hipErrorInvalidValue;
     switch (gemm_kind(a)) {
       case 0: return launch_split_tile<SplitL>(a, s);

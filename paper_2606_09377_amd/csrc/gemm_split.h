@@ -1,11 +1,16 @@
-// The dense backward, forward and IBP steps on split operands (split_bf16.h): the kernels that
-// launch_gemm runs when the layer's split weights are present (GemmArgs.Bs).  Part of gemm.hip.
+// The dense backward, forward and IBP steps on split operands (split_bf16.h).  Part of gemm.hip.
 //
 // A workgroup owns a BM x BN tile of the output, WM x WN waves of (BM / WM) x (BN / WN), in
 // 16 x 16 blocks.  Per K step of 32 the coefficient rows (float32, 128 bytes a row) and the
 // weights' three parts go from global memory straight into double-buffered LDS; a wave splits
 // its coefficient rows into bf16 parts in registers (5.5 vector instructions a value, under
 // the matrix instructions of the other wave of its SIMD) and multiplies.
+//
+// WF: a layer without split weights in memory (GemmArgs.Bs null: the device had no room for them, or
+// the caller wants none) has its float32 weights staged like the coefficients and split by every
+// wave that multiplies them: the same bits, without the memory, at the cost of those
+// instructions (784-1024x6 MLP, 64 inputs: 21.8 against 18.6 ms with split weights and 30.4 on the
+// float32 instructions; one input, a chain on small tiles: 0.97 against 0.64 and 0.89).
 //
 // The coefficients stay float32 in memory (splitting them where they are produced would save
 // those instructions but cost half as much memory again, in traffic and in workspace).
@@ -27,7 +32,8 @@ struct SplitTile {
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, NS = NS_, MINB = MINB_;
   static constexpr int NW = WM * WN, T = 64 * NW;
   static constexpr int MB = BM / WM / 16, NB = BN / WN / 16;   // 16 x 16 blocks of a wave
-  static constexpr int A_FLOATS = BM * 32, B_FLOATS = BN / 16 * SPLIT_BLOCK / 2;
+  static constexpr int A_FLOATS = BM * 32, B_FLOATS = BN / 16 * SPLIT_BLOCK / 2;   // a stage
+  static_assert(BN * 32 <= B_FLOATS, "float32 weights fit the stage of their split parts");
   static constexpr int LDS_FLOATS = NS * (A_FLOATS + B_FLOATS);
 };
 typedef SplitTile<128, 128, 2, 2, 2, 2> SplitL;
@@ -216,7 +222,7 @@ __device__ __forceinline__ void split_epilogue(const GemmArgs &p, f32v4 (&acc)[T
   }
 }
 
-template <class TS, bool FWD, bool AL, bool AFF>
+template <class TS, bool FWD, bool AL, bool AFF, bool WF>
 __global__ __launch_bounds__(TS::T, TS::MINB) void k_gemm_split(const GemmArgs p) {
   constexpr int MB = TS::MB, NB = TS::NB, NS = TS::NS, NW = TS::NW;
   __shared__ __attribute__((aligned(16))) float lds[TS::LDS_FLOATS];
@@ -234,8 +240,8 @@ __global__ __launch_bounds__(TS::T, TS::MINB) void k_gemm_split(const GemmArgs p
 
   // One load of a wave fills 1 KB of LDS in lane order: 8 coefficient rows (lane = row, 16-byte
   // chunk; the chunk that lands in a slot is swizzled by lds_swz, the swizzle applied on the
-  // fetch side) or one part of a 16-column block of weights. 
-  constexpr int AI = TS::BM / 8, BI = 3 * (TS::BN / 16);
+  // fetch side), or as many rows of float32 weights, or one part of a 16-column block of weights.
+  constexpr int AI = TS::BM / 8, BI = WF ? TS::BN / 8 : 3 * (TS::BN / 16);
   constexpr int AQ = (AI + NW - 1) / NW, BQ = (BI + NW - 1) / NW;
   static_assert(AI % NW == 0 || AI < NW, "loads spread evenly over the waves");
   const int kblocks = p.K / 32;
@@ -246,7 +252,8 @@ __global__ __launch_bounds__(TS::T, TS::MINB) void k_gemm_split(const GemmArgs p
     a_off[q] = (uint32_t)row * (uint32_t)(p.lda * 4) + ((lane & 7) ^ lds_swz<32>(row)) * 16;
   }
   const float *a_tile = p.A + (int64_t)m0 * p.lda;
-  const uint16_t *b_tile = p.Bs + (int64_t)(n0 / 16) * kblocks * SPLIT_BLOCK;
+  const float *w_tile = p.Bt + (int64_t)n0 * p.ldb;
+  const uint16_t *b_tile = WF ? nullptr : p.Bs + (int64_t)(n0 / 16) * kblocks * SPLIT_BLOCK;
   auto issue = [&](int kt, int buf) {
 #pragma unroll
     for (int q = 0; q < AQ; ++q) {
@@ -256,9 +263,15 @@ __global__ __launch_bounds__(TS::T, TS::MINB) void k_gemm_split(const GemmArgs p
 #pragma unroll
     for (int q = 0; q < BQ; ++q) {
       const int i = min(q * NW + wave, BI - 1);
-      const int nb = i / 3, part = i - 3 * nb;
-      dma16(b_tile + ((int64_t)nb * kblocks + kt) * SPLIT_BLOCK + part * 512, (uint32_t)lane * 16,
-            Bs + buf * TS::B_FLOATS + i * 256);
+      if constexpr (WF) {
+        const int row = i * 8 + (lane >> 3);
+        dma16(w_tile + kt * 32, (uint32_t)row * (uint32_t)(p.ldb * 4) + ((lane & 7) ^ lds_swz<32>(row)) * 16,
+              Bs + buf * TS::B_FLOATS + i * 256);
+      } else {
+        const int nb = i / 3, part = i - 3 * nb;
+        dma16(b_tile + ((int64_t)nb * kblocks + kt) * SPLIT_BLOCK + part * 512, (uint32_t)lane * 16,
+              Bs + buf * TS::B_FLOATS + i * 256);
+      }
     }
   };
   constexpr int LPT = AQ + BQ;   // loads of a wave per K step
@@ -272,6 +285,8 @@ __global__ __launch_bounds__(TS::T, TS::MINB) void k_gemm_split(const GemmArgs p
   const int r16 = lane & 15, g4 = lane >> 4, sw = lds_swz<32>(r16);
   const uint32_t abs_mask = AFF && p.abs_b ? 0x80008000u : 0u;
   const int ch0 = ((2 * g4) ^ sw) * 4, ch1 = ((2 * g4 + 1) ^ sw) * 4;
+  // the lane's part of the wave's first column block in a stage
+  const float *b_lane = Bs + (WF ? (wn * NB * 16 + r16) * 32 : (wn * NB * 192 + lane) * 4);
 #pragma unroll
   for (int s = 0; s < NS - 1; ++s)
     if (s < KT) issue(s, s);
@@ -281,9 +296,8 @@ __global__ __launch_bounds__(TS::T, TS::MINB) void k_gemm_split(const GemmArgs p
     // barrier that publishes step kt + 1 also frees step kt's stage for step kt + NS.  (Two
     // register sets, the loop unrolled by two, so that no set is copied.)
     const float *as = As + (wm * (TS::BM / TS::WM) + r16) * 32;
-    const bf16x8 *bs = reinterpret_cast<const bf16x8 *>(Bs) + wn * NB * 192 + lane;
     auto read = [&](int buf, SplitRaw<MB, NB> &r) {
-      split_read<MB, NB, AFF>(r, as + buf * TS::A_FLOATS, ch0, ch1, bs + buf * (TS::B_FLOATS / 4), abs_mask);
+      split_read<MB, NB, AFF, WF>(r, as + buf * TS::A_FLOATS, ch0, ch1, b_lane + buf * TS::B_FLOATS, abs_mask);
     };
     auto landed = [&](int later) {   // with `later` steps requested after the one waited for
       if (NS >= 4 && later >= 2) wait_vmcnt<(NS >= 4 ? 2 : 0) * LPT>();
@@ -323,8 +337,7 @@ __global__ __launch_bounds__(TS::T, TS::MINB) void k_gemm_split(const GemmArgs p
       barrier_only();   // every wave's part of step kt is in LDS, and step kt - 1's stage is free
       if (kt + NS - 1 < KT) issue(kt + NS - 1, cur + NS - 1 >= NS ? cur - 1 : cur + NS - 1);
       const float *as = As + cur * TS::A_FLOATS + (wm * (TS::BM / TS::WM) + r16) * 32;
-      const bf16x8 *bs = reinterpret_cast<const bf16x8 *>(Bs + cur * TS::B_FLOATS) + wn * NB * 192 + lane;
-      split_step<MB, NB, AFF>(as, ch0, ch1, bs, nj, abs_mask, hi, lo);
+      split_step<MB, NB, AFF, WF>(as, ch0, ch1, b_lane + cur * TS::B_FLOATS, nj, abs_mask, hi, lo);
       cur = cur + 1 == NS ? 0 : cur + 1;
     }
   }
@@ -333,7 +346,7 @@ __global__ __launch_bounds__(TS::T, TS::MINB) void k_gemm_split(const GemmArgs p
     const float unscale = split_finish<MB, NB>(
         hi, lo, col0, p.N, g4, [&](int i) { return m0 + row0 + 16 * i < p.M; },
         [&](int i, int j) {
-          return mma_float32(a_tile + (int64_t)(row0 + 16 * i) * p.lda, p.Bt + (int64_t)(col0 + 16 * j + r16) * p.ldb,
+          return mma_float32(a_tile + (int64_t)(row0 + 16 * i) * p.lda, w_tile + (int64_t)(col0 - n0 + 16 * j + r16) * p.ldb,
                              p.K_real, g4, AFF && p.abs_b ? 0x7fffffffu : 0xffffffffu, f32v4{0.f, 0.f, 0.f, 0.f});
         });
 #pragma unroll
@@ -370,24 +383,30 @@ hipError_t launch_split_weights(const float *src, int64_t ld, int64_t N, int64_t
   return hipGetLastError();
 }
 
-template <class TS>
+template <class TS, bool WF>
 static hipError_t launch_split_tile(const GemmArgs &a, hipStream_t s) {
   const int64_t grid = (int64_t)((a.M + TS::BM - 1) / TS::BM) * (a.N_pad / TS::BN);
   if (grid > 0x7fffffff) return hipErrorInvalidValue;
   const dim3 g((unsigned)grid), t(TS::T);
   if (a.mode == EPI_AFFINE)
-    hipLaunchKernelGGL((k_gemm_split<TS, false, false, true>), g, t, 0, s, a);
+    hipLaunchKernelGGL((k_gemm_split<TS, false, false, true, WF>), g, t, 0, s, a);
   else if (a.mode == EPI_FORWARD)
-    hipLaunchKernelGGL((k_gemm_split<TS, true, true, false>), g, t, 0, s, a);
+    hipLaunchKernelGGL((k_gemm_split<TS, true, true, false, WF>), g, t, 0, s, a);
   else if (a.alpha || a.pre)
-    hipLaunchKernelGGL((k_gemm_split<TS, false, true, false>), g, t, 0, s, a);
+    hipLaunchKernelGGL((k_gemm_split<TS, false, true, false, WF>), g, t, 0, s, a);
   else
-    hipLaunchKernelGGL((k_gemm_split<TS, false, false, false>), g, t, 0, s, a);
+    hipLaunchKernelGGL((k_gemm_split<TS, false, false, false, WF>), g, t, 0, s, a);
   return hipGetLastError();
 }
 
-// The split kernels address a tile of coefficient rows by 32-bit byte offsets.
-static bool use_split(const GemmArgs &a) { return a.Bs && a.lda <= (int64_t)1 << 23; }
+template <class TS>
+static hipError_t launch_split_tile(const GemmArgs &a, hipStream_t s) {
+  return a.Bs ? launch_split_tile<TS, false>(a, s) : launch_split_tile<TS, true>(a, s);
+}
+
+// The split kernels address a tile of coefficient or weight rows by 32-bit byte offsets; longer
+// rows are multiplied in float32, like those of a caller who asks for it.
+static bool use_split(const GemmArgs &a) { return !a.float32 && std::max(a.lda, a.ldb) <= (int64_t)1 << 23; }
 
 // 0: SplitL, 3: SplitM, 2: SplitS.  In its own loop (K = 1024, N = 1024) SplitL reaches 228
 // TFLOP/s and SplitM 187; SplitL holds 512 workgroups on the chip at once, so it runs where its

@@ -46,7 +46,9 @@ struct GNode {
   float *Wp = nullptr;         // dense [out][ld(in)] original column order (IBP, spec fold)
   float *Wh = nullptr;         // dense [out][ld(in)] HWC column order when hwc_in (init rows)
   float *Wk = nullptr;         // conv [Co][3][3][Ci]: channels contiguous per tap (init rows)
-  // split copies (see DenseLayer) of Bt, and of Wh / Wp (dense) or Wk (conv)
+  // split copies (split_bf16.h) of Bt, and of Wk (conv; the convolution kernels' weights, null on
+  // the stem and with float32 products) or Wh / Wp (dense; null where there is no room, see
+  // DenseLayer)
   uint16_t *Bs = nullptr, *Ws = nullptr;
   float *b = nullptr;          // bias, zero padded to ld(out) for dense
   std::vector<float> hb;       // host copy of the bias
@@ -131,6 +133,8 @@ void destroy_graph(GraphNet *g) {
   for (auto &n : g->nodes) {
     for (float *p : {n.W, n.Bt, n.Wp, n.Wh, n.Wk, n.b})
       if (p) (void)hipFree(p);
+    for (uint16_t *p : {n.Bs, n.Ws})
+      if (p && n.op == VCR_CONV2D) (void)hipFree(p);
   }
   if (g->bias_arena) (void)hipFree(g->bias_arena);
   if (g->param_arena) (void)hipFree(g->param_arena);
@@ -779,6 +783,13 @@ vcr_status graph_load(vcr_ctx *c, const vcr_node *nodes, int32_t n, const int32_
       HIP_TRY(c, hipMalloc(&gn.Bt, (size_t)gn.Ci_pad * 9 * Co * 4));
       c->net_bytes += (size_t)gn.Ci_pad * 9 * Co * 4;
       HIP_TRY(c, launch_repack_convt(gn.W, Co, Ci, gn.Ci_pad, gn.Bt, s));
+      if (Ci % 32 == 0 && c->net_products != VCR_PRODUCTS_FLOAT32) {   // not the stem
+        HIP_TRY(c, hipMalloc(&gn.Bs, (size_t)gn.Ci_pad * 9 * Co * 6));
+        HIP_TRY(c, launch_split_weights(gn.Bt, 9 * (int64_t)Co, gn.Ci_pad, 9 * (int64_t)Co, gn.Bs, s));
+        HIP_TRY(c, hipMalloc(&gn.Ws, wn * 6));
+        HIP_TRY(c, launch_split_weights(gn.Wk, 9 * (int64_t)Ci, Co, 9 * (int64_t)Ci, gn.Ws, s));
+        c->net_bytes += (size_t)gn.Ci_pad * 9 * Co * 6 + wn * 6;
+      }
     } else if (d.op == VCR_DENSE) {
       const int64_t nin = d.in0 >= 0 ? g->nodes[d.in0].numel : g->n0;
       const int64_t nout = d.out_features;
@@ -854,10 +865,6 @@ vcr_status graph_load(vcr_ctx *c, const vcr_node *nodes, int32_t n, const int32_
     std::vector<SplitItem> items;
     for (int i = 0; i + 1 < n; ++i) {   // the output node is no product's operand
       GNode &gn = g->nodes[i];
-      if (gn.op == VCR_CONV2D && gn.Ci % 32 == 0 && gn.C % 32 == 0) {   // not the stem
-        items.push_back({gn.Bt, 9 * (int64_t)gn.C, gn.Ci_pad, 9 * (int64_t)gn.C, &gn.Bs});
-        items.push_back({gn.Wk, 9 * (int64_t)gn.Ci, gn.C, 9 * (int64_t)gn.Ci, &gn.Ws});
-      }
       if (gn.op != VCR_DENSE) continue;
       items.push_back({gn.Bt, gn.ld_out, gn.ld_in, gn.ld_out, &gn.Bs});
       items.push_back({gn.hwc_in ? gn.Wh : gn.Wp, gn.ld_in, gn.ld_out, gn.ld_in, &gn.Ws});
@@ -1115,6 +1122,7 @@ vcr_status run_pass(vcr_ctx *c, GraphNet *g, GBufs &bf, const PassPlan &pp, int 
         ga.lda = nd.ld_out;
         ga.Bt = nd.Bt;
         ga.Bs = nd.Bs;
+        ga.float32 = c->net_products == VCR_PRODUCTS_FLOAT32;
         ga.ldb = nd.ld_out;
         ga.N = (int32_t)g->nodes[nd.in0].numel;
         ga.K_real = (int32_t)nd.numel;
@@ -1224,6 +1232,7 @@ vcr_status run_forward(vcr_ctx *c, GraphNet *g, GBufs &bf, int u0, int units, in
         ga.lda = nd.ld_in;
         ga.Bt = nd.hwc_in ? nd.Wh : nd.Wp;
         ga.Bs = nd.Ws;
+        ga.float32 = c->net_products == VCR_PRODUCTS_FLOAT32;
         ga.ldb = nd.ld_in;
         ga.N = (int32_t)nd.numel;
         ga.K_real = (int32_t)g->nodes[nd.in0].numel;

@@ -43,9 +43,10 @@ struct GemmArgs {
   int32_t K;           // multiple of BK (padded)
   int32_t N_pad;       // multiple of BN
   int32_t mode;        // EpiMode
-  // the same weights split into bf16 parts (split_bf16.h), or null: with them the step runs on
-  // the bf16 matrix cores, over the real columns and contraction length only
+  // the same weights split into bf16 parts (split_bf16.h), or null: the kernel splits Bt then,
+  // with the same results
   const uint16_t *Bs;
+  int32_t float32;     // multiply in float32 instead (VCR_PRODUCTS_FLOAT32)
   int32_t N, K_real;   // real columns and contraction length (the rest is zero padding)
   // relax epilogue: out = relax(A Bt^T) with the per-unit parameters of the next ReLU
   float *out;

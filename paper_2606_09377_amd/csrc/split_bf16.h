@@ -135,16 +135,31 @@ __device__ __forceinline__ void split_mma1(const Split8 &a, const Split8 &w, f32
 // lane without bank conflicts.
 constexpr int SPLIT_BLOCK = 3 * 64 * 8;   // bf16 values of one 16 x 32 block
 
+// Column block j of a wave's weights from LDS: ws is the lane's part of the first block, its three
+// split parts, or (WF) its first row of float32 weights, laid out as the coefficients below and
+// split here, into the same bits.
+template <bool WF>
+__device__ __forceinline__ Split8 split_weights(const void *ws, int j, int ch0, int ch1) {
+  if constexpr (WF) {
+    const float *w = static_cast<const float *>(ws) + j * 512;
+    return split8(*reinterpret_cast<const f32v4 *>(w + ch0) * SPLIT_SCALE,
+                  *reinterpret_cast<const f32v4 *>(w + ch1) * SPLIT_SCALE);
+  } else {
+    const bf16x8 *w = static_cast<const bf16x8 *>(ws) + j * 192;
+    return Split8{w[0], w[64], w[128]};
+  }
+}
+
 // One K step of a wave from LDS: MB row blocks of coefficients (as: the lane's first row, 32
 // floats a row, 16 rows a block, the lane's two 16-byte chunks at ch0 and ch1) times NB column
-// blocks of weights (ws: the lane's part of the first block), the first nj of which hold real
+// blocks of weights (ws, see split_weights), the first nj of which hold real
 // columns (wave-uniform).  The first column block multiplies each row block as soon as it is
 // split; every block's weights are read from LDS while the block before is multiplied.
-template <int MB, int NB, bool ABS>
-__device__ __forceinline__ void split_step(const float *as, int ch0, int ch1, const bf16x8 *ws, int nj,
+template <int MB, int NB, bool ABS, bool WF = false>
+__device__ __forceinline__ void split_step(const float *as, int ch0, int ch1, const void *ws, int nj,
                                            uint32_t abs_mask, f32v4 (&hi)[MB][NB], f32v4 (&lo)[MB][NB]) {
   auto load_w = [&](int j) {
-    const Split8 w{ws[j * 192], ws[j * 192 + 64], ws[j * 192 + 128]};
+    const Split8 w = split_weights<WF>(ws, j, ch0, ch1);
     return ABS ? split_abs(w, abs_mask) : w;
   };
   f32v4 x[MB], y[MB];
@@ -179,8 +194,8 @@ struct SplitRaw {
   f32v4 x[MB], y[MB];
   Split8 w[NB];
 };
-template <int MB, int NB, bool ABS>
-__device__ __forceinline__ void split_read(SplitRaw<MB, NB> &r, const float *as, int ch0, int ch1, const bf16x8 *ws,
+template <int MB, int NB, bool ABS, bool WF>
+__device__ __forceinline__ void split_read(SplitRaw<MB, NB> &r, const float *as, int ch0, int ch1, const void *ws,
                                            uint32_t abs_mask) {
 #pragma unroll
   for (int i = 0; i < MB; ++i) {
@@ -189,7 +204,7 @@ __device__ __forceinline__ void split_read(SplitRaw<MB, NB> &r, const float *as,
   }
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
-    const Split8 w{ws[j * 192], ws[j * 192 + 64], ws[j * 192 + 128]};
+    const Split8 w = split_weights<WF>(ws, j, ch0, ch1);
     r.w[j] = ABS ? split_abs(w, abs_mask) : w;
   }
 }

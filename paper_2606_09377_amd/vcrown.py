@@ -25,7 +25,7 @@ OPS = {"dense": 0, "conv2d": 1, "relu": 2, "add": 3, "flatten": 4}
 # values of OPT_LAMBDA_RULE (the lower slope of unstable ReLU neurons)
 LAMBDA_RULES = {"adaptive": 0, "zero": 1, "one": 2, "same_slope": 3}
 # values of OPT_PRODUCTS (how the networks loaded from then on multiply)
-PRODUCTS = {"split": 0, "float32": 1}
+PRODUCTS = {"split": 0, "float32": 1, "split_no_copies": 2}
 MAX_SPLITS = 64   # VCR_MAX_SPLITS
 
 

@@ -1,6 +1,5 @@
 """The products on split bf16 operands: every tile shape at widths around its edges against the
-oracle, the same bits from every shape, and the float32 kernels where the device has no room for
-the split weights."""
+oracle, and the same bits from every shape, with split weights in memory and without."""
 import contextlib
 
 import numpy as np
@@ -83,8 +82,17 @@ def short_memory():
         torch.cuda.empty_cache()
 
 
-def test_float32_kernels_when_memory_is_short():
-    """The bounds then come from the float32 kernels, within the parity tolerance."""
+def same_bits(a, b):
+    """Results as gpu_crown's (and what follows them) are equal bit for bit."""
+    flat = lambda r: [x for v in r for x in (v if isinstance(v, (list, tuple)) else [v])]  # noqa: E731
+    a, b = flat(flat(a)), flat(flat(b))
+    assert len(a) == len(b) > 2
+    for x, y in zip(a, b):
+        assert np.array_equal(x, y)
+
+
+def test_same_bits_when_memory_is_short():
+    """No split weights are kept then; the bounds are the same bits."""
     wl = random_mlp(951, [120, 200, 180, 77, 300, 9], 2, 0.03)
     with_split = gpu_ctx(wl.net)
     want = gpu_crown(with_split, wl)
@@ -94,7 +102,8 @@ def test_float32_kernels_when_memory_is_short():
         lb, ub, layers = gpu_crown(ctx, wl)
     for b in range(2):
         check_input(wl.net, wl.x0[b], wl.eps, wl.C[b], lb[b], ub[b], [(l[b], u[b]) for l, u in layers])
-        assert_close(lb[b], want[0][b].astype(np.float64), "float32 and split products")
+        assert_close(lb[b], want[0][b].astype(np.float64), "with and without split weights")
+    same_bits((lb, ub, layers), want)
 
 
 def odd_resnet(seed, hw, c1, c2, fc, n_out):
@@ -111,10 +120,9 @@ def odd_resnet(seed, hw, c1, c2, fc, n_out):
 # an odd image side (window positions and rows that fill no 96- or 128-row tile), the 64-column
 # blocks of 32 and 64 channels and the 128-column ones of 128, and stride 1 and 2
 @pytest.mark.parametrize("hw,c1,c2,fc", [(7, 32, 64, 33), (5, 64, 128, 20)])
-def test_convolutions_split_and_float32(hw, c1, c2, fc):
-    """Bounds, slope gradients of a convolutional network on split operands and, with memory
-    short, on the float32 kernels: each within the parity tolerance of the oracle, the gradients
-    of the two within the gradient's tolerance of each other."""
+def test_convolutions_with_and_without_copies(hw, c1, c2, fc):
+    """Bounds and slope gradients of a convolutional network with and, memory being short, without
+    split dense weights: within the parity tolerance of the oracle, and the same bits."""
     import torch
     wl = odd_resnet(960 + hw, hw, c1, c2, fc, 5)
     with_split = gpu_ctx(wl.net)
@@ -135,3 +143,4 @@ def test_convolutions_split_and_float32(hw, c1, c2, fc):
             check_input(wl.net, wl.x0[b], wl.eps, wl.C[b], lb[b], ub[b], [(l[b], u[b]) for l, u in layers])
     _assert_grad_close(a[3], f[3].astype(np.float64), "gradients")
     assert np.count_nonzero(f[3]) > 0
+    same_bits(a, f)
