@@ -142,8 +142,10 @@ enum {
 /* Values of VCR_OPT_PRODUCTS: SPLIT (default), on the bf16 matrix cores with operands split into
  * bf16 values; FLOAT32, on the float32 matrix cores (about 1.6 times slower on large networks);
  * SPLIT_NO_COPIES, SPLIT's bits without the split copies of dense weights (6 bytes a weight and
- * operand layout, vcr_stats.net_bytes), about 1.2 times slower, 1.5 on single inputs: what SPLIT does by itself where the copies would
- * leave less than an eighth of the device's memory free or a workspace needs their room. */
+ * operand layout, vcr_stats.net_bytes), about 1.2 times slower, 1.5 on single inputs: what SPLIT
+ * does by itself while the copies would leave less than an eighth of the device's memory free, and
+ * once an allocation of the context has taken their place (a later call makes them again when
+ * there is room). */
 enum {
   VCR_PRODUCTS_SPLIT = 0,
   VCR_PRODUCTS_FLOAT32 = 1,

@@ -128,14 +128,8 @@ vcr_status ensure_ws(vcr_ctx *c, size_t bytes) {
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   free_ws(c);
   void *p = nullptr;
-  hipError_t e = hipMalloc(&p, bytes);
-  if (e != hipSuccess && c->split_base) {   // the split weights make room
-    (void)hipGetLastError();
-    drop_split_operands(c);
-    e = hipMalloc(&p, bytes);
-  }
+  const hipError_t e = device_alloc(c, &p, bytes);
   if (e != hipSuccess) {
-    (void)hipGetLastError();
     return fail(c, VCR_ERR_OOM, "hipMalloc(%llu) failed: %s", (unsigned long long)bytes, hipGetErrorString(e));
   }
   c->ws.base = static_cast<char *>(p);
@@ -147,12 +141,16 @@ vcr_status ensure_ws(vcr_ctx *c, size_t bytes) {
   return VCR_OK;
 }
 
-vcr_status split_operands(vcr_ctx *c, const std::vector<SplitItem> &items) {
+namespace {
+size_t split_size(const SplitItem &it) { return al(sizeof(uint16_t) * 3 * (size_t)it.N * (size_t)it.K); }
+
+// the copies, if device memory is there for them and `spare` more bytes
+vcr_status make_split_copies(vcr_ctx *c, size_t spare) {
   size_t bytes = 0, free_b = 0, total_b = 0;
-  for (const SplitItem &it : items) bytes += al(sizeof(uint16_t) * 3 * (size_t)it.N * (size_t)it.K);
-  if (bytes == 0 || c->net_products != VCR_PRODUCTS_SPLIT) return VCR_OK;
+  for (const SplitItem &it : c->split_items) bytes += split_size(it);
+  if (bytes == 0 || c->split_base || c->net_products != VCR_PRODUCTS_SPLIT) return VCR_OK;
   HIP_TRY(c, hipMemGetInfo(&free_b, &total_b));
-  if (bytes + total_b / 8 > free_b) return VCR_OK;
+  if (bytes + spare > free_b) return VCR_OK;
   void *base = nullptr;
   if (hipMalloc(&base, bytes) != hipSuccess) {
     (void)hipGetLastError();
@@ -160,24 +158,31 @@ vcr_status split_operands(vcr_ctx *c, const std::vector<SplitItem> &items) {
   }
   c->split_base = base;
   c->split_bytes = bytes;
+  c->net_bytes += bytes;
+  ++c->net_epoch;   // a recorded graph runs without them
   size_t off = 0;
-  for (const SplitItem &it : items) {
+  for (const SplitItem &it : c->split_items) {
     *it.dst = reinterpret_cast<uint16_t *>(static_cast<char *>(base) + off);
-    c->split_ptrs.push_back(it.dst);
     const hipError_t e = launch_split_weights(it.src, it.ld, it.N, it.K, *it.dst, c->stream);
     if (e != hipSuccess) {
-      drop_split_operands(c);
+      drop_split_copies(c);
       return fail(c, VCR_ERR_DEVICE, "launch_split_weights: %s", hipGetErrorString(e));
     }
-    off += al(sizeof(uint16_t) * 3 * (size_t)it.N * (size_t)it.K);
+    off += split_size(it);
   }
-  c->net_bytes += bytes;
   return VCR_OK;
 }
+}  // namespace
 
-void drop_split_operands(vcr_ctx *c) {
-  for (uint16_t **p : c->split_ptrs) *p = nullptr;
-  c->split_ptrs.clear();
+vcr_status make_split_copies(vcr_ctx *c) {
+  size_t free_b = 0, total_b = 0;
+  if (c->split_items.empty() || c->split_base || c->net_products != VCR_PRODUCTS_SPLIT) return VCR_OK;
+  HIP_TRY(c, hipMemGetInfo(&free_b, &total_b));
+  return make_split_copies(c, total_b / 8);
+}
+
+void drop_split_copies(vcr_ctx *c) {
+  for (const SplitItem &it : c->split_items) *it.dst = nullptr;
   if (!c->split_base) return;
   (void)hipDeviceSynchronize();   // launches on any stream may still read them
   (void)hipFree(c->split_base);
@@ -185,6 +190,36 @@ void drop_split_operands(vcr_ctx *c) {
   c->net_bytes -= std::min(c->net_bytes, c->split_bytes);
   c->split_bytes = 0;
   ++c->net_epoch;   // a recorded graph holds their addresses
+}
+
+void forget_split_operands(vcr_ctx *c) {
+  drop_split_copies(c);
+  c->split_items.clear();
+}
+
+vcr_status regain_split_copies(vcr_ctx *c) {
+  if (c->split_base || c->split_items.empty() || c->net_products != VCR_PRODUCTS_SPLIT) return VCR_OK;
+  HIP_TRY(c, hipSetDevice(c->device));
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) (void)hipGetLastError();
+  return cap == hipStreamCaptureStatusNone ? make_split_copies(c) : VCR_OK;   // no allocation in a capture
+}
+
+hipError_t device_alloc(vcr_ctx *c, void **p, size_t bytes) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e == hipSuccess) return e;
+  (void)hipGetLastError();
+  size_t free_b = 0, total_b = 0;
+  // (the driver gives somewhat more than it reports as free)
+  if (!c->split_base || hipMemGetInfo(&free_b, &total_b) != hipSuccess ||
+      free_b + total_b / 64 + c->split_bytes < bytes)
+    return e;
+  drop_split_copies(c);
+  e = hipMalloc(p, bytes);
+  if (e == hipSuccess) return e;
+  (void)hipGetLastError();
+  (void)make_split_copies(c, 0);   // that did not help: as they were
+  return e;
 }
 
 namespace {
@@ -344,7 +379,7 @@ void vcr_destroy(vcr_ctx *c) {
   if (c->device >= 0) {
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
-    drop_split_operands(c);
+    forget_split_operands(c);
     free_layers(c);
     free_ws(c);
     if (c->d_counters) (void)hipFree(c->d_counters);
@@ -437,7 +472,7 @@ vcr_status vcr_load_net(vcr_ctx *c, const vcr_node *nodes, int32_t n, const int3
     if (c->device >= 0) {
       HIP_TRY(c, hipSetDevice(c->device));
       HIP_TRY(c, hipStreamSynchronize(c->stream));
-      drop_split_operands(c);
+      forget_split_operands(c);
       free_layers(c);
       free_ws(c);
     }
@@ -452,7 +487,7 @@ vcr_status vcr_load_net(vcr_ctx *c, const vcr_node *nodes, int32_t n, const int3
   if (st != VCR_OK) return st;
   if (c->device >= 0) {
     HIP_TRY(c, hipSetDevice(c->device));
-    drop_split_operands(c);
+    forget_split_operands(c);
   }
   destroy_graph(c->graph);
   c->graph = nullptr;
@@ -535,13 +570,12 @@ vcr_status vcr_load_net(vcr_ctx *c, const vcr_node *nodes, int32_t n, const int3
   c->net_bytes = 0;
   for (const DenseLayer &L : c->layers)
     c->net_bytes += sizeof(float) * (2 * (uint64_t)L.ld_in * L.ld_out + (uint64_t)L.ld_out);
-  std::vector<SplitItem> items;
   for (size_t j = 0; j + 1 < c->layers.size(); ++j) {   // the last layer is no product's operand
     DenseLayer &L = c->layers[j];
-    items.push_back({L.Bt, L.ld_out, L.ld_in, L.ld_out, &L.Bs});
-    items.push_back({L.Wp, L.ld_in, L.ld_out, L.ld_in, &L.Ws});
+    c->split_items.push_back({L.Bt, L.ld_out, L.ld_in, L.ld_out, &L.Bs});
+    c->split_items.push_back({L.Wp, L.ld_in, L.ld_out, L.ld_in, &L.Ws});
   }
-  st = split_operands(c, items);
+  st = make_split_copies(c);
   if (st != VCR_OK) return st;
   HIP_TRY(c, hipDeviceSynchronize());
   c->loaded = true;
@@ -1062,7 +1096,7 @@ vcr_status crown_impl(vcr_ctx *c, const float *x0, int32_t B, float eps, const f
       if (c->root_cache) HIP_TRY(c, hipFree(c->root_cache));
       c->root_cache = nullptr;
       c->root_cache_cap = 0;
-      HIP_TRY(c, hipMalloc(&c->root_cache, sizeof(float) * cache_floats));
+      HIP_TRY(c, device_alloc(c, reinterpret_cast<void **>(&c->root_cache), sizeof(float) * cache_floats));
       c->root_cache_cap = cache_floats;
     }
     st = cache_copy(true);
@@ -1202,6 +1236,8 @@ vcr_status vcr_crown_bounds(vcr_ctx *c, const float *x0, int32_t B, float eps, c
   }
   st = check_finite_inputs(c, x0, B, C, m);
   if (st != VCR_OK) return st;
+  st = regain_split_copies(c);
+  if (st != VCR_OK) return st;
   auto run = [&]() {
     return c->graph ? graph_crown(c, x0, B, eps, C, m, splits, lb, ub) : crown_impl(c, x0, B, eps, C, m, splits, lb, ub);
   };
@@ -1227,6 +1263,7 @@ vcr_status vcr_crown_bounds(vcr_ctx *c, const float *x0, int32_t B, float eps, c
     c->gexec = nullptr;
   }
   if (!c->cap_stream) HIP_TRY(c, hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking));
+  key[12] = c->net_epoch;   // the split weights may have made room for the workspace
   key[13] = (uint64_t)(uintptr_t)c->ws.base;
   key[14] = (uint64_t)c->ws.cap;
   hipStream_t user = c->stream;
@@ -1322,6 +1359,8 @@ vcr_status vcr_ibp_bounds(vcr_ctx *c, const float *x0, int32_t B, float eps, con
   if (c->device < 0) return fail(c, VCR_ERR_STATE, "validation-only context: no device work");
   st = check_finite_inputs(c, x0, B, C, m);
   if (st != VCR_OK) return st;
+  st = regain_split_copies(c);
+  if (st != VCR_OK) return st;
   if (c->graph) return after_call(c, graph_ibp(c, x0, B, eps, C, m, lb, ub), t0);
   HIP_TRY(c, hipSetDevice(c->device));
   const int L = (int)c->layers.size();
@@ -1380,6 +1419,8 @@ vcr_status vcr_alpha_crown_bounds(vcr_ctx *c, const float *x0, int32_t B, float 
   if ((int64_t)B * 2 * m * ac.n_total > ((int64_t)1 << 40)) return fail(c, VCR_ERR_SHAPE, "alpha tensors too large");
   st = check_finite_inputs(c, x0, B, C, m);
   if (st != VCR_OK) return st;
+  st = regain_split_copies(c);
+  if (st != VCR_OK) return st;
   if (c->graph) return after_call(c, graph_alpha(c, x0, B, eps, C, m, o, ac.n_total, lb, ub), t0);
   return after_call(c, crown_impl(c, x0, B, eps, C, m, nullptr, lb, ub, &ac), t0);
 }
@@ -1433,7 +1474,7 @@ vcr_status bab_reserve(vcr_ctx *c, size_t bytes) {
   if (c->bab_buf) HIP_TRY(c, hipFree(c->bab_buf));
   c->bab_buf = nullptr;
   c->bab_cap = 0;
-  HIP_TRY(c, hipMalloc(&c->bab_buf, bytes));
+  HIP_TRY(c, device_alloc(c, &c->bab_buf, bytes));
   c->bab_cap = bytes;
   return VCR_OK;
 }
@@ -1458,6 +1499,8 @@ vcr_status vcr_beta_crown_bounds(vcr_ctx *c, const float *x0, float eps, const f
   st = check_beta_opts(c, opts);
   if (st != VCR_OK) return st;
   st = check_finite_inputs(c, x0, 1, C, m);
+  if (st != VCR_OK) return st;
+  st = regain_split_copies(c);
   if (st != VCR_OK) return st;
   AlphaCall ac = alpha_call_of(c, *opts, true);
   if (c->graph)
@@ -1491,6 +1534,8 @@ vcr_status vcr_bab_verify(vcr_ctx *c, const float *x0, float eps, const float *C
       return fail(c, VCR_ERR_ARG, "split order entry %d out of range", k);
   if (c->device < 0) return fail(c, VCR_ERR_STATE, "validation-only context: no device work");
   st = check_finite_inputs(c, x0, 1, C, m);
+  if (st != VCR_OK) return st;
+  st = regain_split_copies(c);
   if (st != VCR_OK) return st;
   HIP_TRY(c, hipSetDevice(c->device));
   hipStream_t s = c->stream;

@@ -29,8 +29,15 @@ struct DenseLayer {
   float *b = nullptr;    // ld_out, zero padded
   // split copies (split_bf16.h) of Bt and Wp, the operands of the backward and of the forward
   // and IBP products; null on the last layer (never a product's operand) and where there are
-  // none (split_operands): the kernels then split Bt and Wp, with the same results
+  // none (make_split_copies): the kernels then split Bt and Wp, with the same results
   uint16_t *Bs = nullptr, *Ws = nullptr;
+};
+
+// A weight operand [N][K] (float32, pitch ld) to be split into *dst.
+struct SplitItem {
+  const float *src;
+  int64_t ld, N, K;
+  uint16_t **dst;
 };
 
 struct Workspace {
@@ -41,6 +48,7 @@ struct Workspace {
 }  // namespace vcr_internal
 
 using vcr_internal::DenseLayer;
+using vcr_internal::SplitItem;
 using vcr_internal::Workspace;
 
 struct vcr_ctx {
@@ -66,11 +74,11 @@ struct vcr_ctx {
   // workspace
   Workspace ws;
   uint64_t peak_ws = 0;
-  // split weight operands: one allocation, and the layers' pointers into it (set to null when
-  // it is given back)
+  // split weight operands: what the loaded network would have split, and the one allocation that
+  // holds them (null while there is none)
+  std::vector<SplitItem> split_items;
   void *split_base = nullptr;
   uint64_t split_bytes = 0;
-  std::vector<uint16_t **> split_ptrs;
   int32_t net_products = 0; // VCR_PRODUCTS_* of the loaded network
   uint64_t net_bytes = 0;   // device memory holding the loaded network (weights in their layouts)
   // last call
@@ -179,18 +187,20 @@ T *take(vcr_ctx *c, size_t count) {
 
 vcr_status ensure_ws(vcr_ctx *c, size_t bytes);
 
-// A weight operand [N][K] (float32, pitch ld) to be split into *dst.
-struct SplitItem {
-  const float *src;
-  int64_t ld, N, K;
-  uint16_t **dst;
-};
-// Splits the operands of a network being loaded.  The copies cost 6 bytes a weight and layout
-// beside the float32 weights, which stay, and save time only (784-1024x6 MLP, 64 inputs: 18.6 against 21.8 ms):
-// there are none where the caller wants none, where less than an eighth of the device's memory
-// would remain free beside them, and once a workspace has needed the room (ensure_ws).
-vcr_status split_operands(vcr_ctx *c, const std::vector<SplitItem> &items);
-void drop_split_operands(vcr_ctx *c);
+// The split copies of the dense operands of the loaded network (c->split_items; none are made for
+// other VCR_OPT_PRODUCTS than VCR_PRODUCTS_SPLIT).  They cost 6 bytes a weight and layout beside the
+// float32 weights, which stay, and save time only (784-1024x6 MLP, 64 inputs: 18.6 against 21.8 ms,
+// the same bits): they are made where an eighth of the device's memory stays free beside them.  An
+// allocation of this context that fails and would fit in their place takes it (device_alloc; not
+// one of another context or library), and a later call makes them again when there is room.
+vcr_status make_split_copies(vcr_ctx *c);
+void drop_split_copies(vcr_ctx *c);
+// Forgets the network's operands too (before its weights are freed or replaced).
+void forget_split_operands(vcr_ctx *c);
+// Start of a call that may allocate: makes missing copies if there is room now.
+vcr_status regain_split_copies(vcr_ctx *c);
+// hipMalloc, in the place of the split copies if it fails beside them.
+hipError_t device_alloc(vcr_ctx *c, void **p, size_t bytes);
 
 namespace vcr {
 // Resolves the device address of the allocation-free scratch on c's device (current) into

@@ -862,18 +862,20 @@ vcr_status graph_load(vcr_ctx *c, const vcr_node *nodes, int32_t n, const int32_
     HIP_TRY(c, hipMemcpy(g->d_relu_info, info.data(), info.size() * sizeof(int32_t), hipMemcpyHostToDevice));
   }
   if (dev) {
-    std::vector<SplitItem> items;
     for (int i = 0; i + 1 < n; ++i) {   // the output node is no product's operand
       GNode &gn = g->nodes[i];
       if (gn.op != VCR_DENSE) continue;
-      items.push_back({gn.Bt, gn.ld_out, gn.ld_in, gn.ld_out, &gn.Bs});
-      items.push_back({gn.hwc_in ? gn.Wh : gn.Wp, gn.ld_in, gn.ld_out, gn.ld_in, &gn.Ws});
+      c->split_items.push_back({gn.Bt, gn.ld_out, gn.ld_in, gn.ld_out, &gn.Bs});
+      c->split_items.push_back({gn.hwc_in ? gn.Wh : gn.Wp, gn.ld_in, gn.ld_out, gn.ld_in, &gn.Ws});
     }
-    const vcr_status st = split_operands(c, items);
-    if (st != VCR_OK) return st;
+    const vcr_status st = make_split_copies(c);
+    if (st != VCR_OK) {
+      forget_split_operands(c);
+      return st;
+    }
     const hipError_t e = hipDeviceSynchronize();
     if (e != hipSuccess) {
-      drop_split_operands(c);
+      forget_split_operands(c);
       return fail(c, VCR_ERR_DEVICE, "hipDeviceSynchronize: %s", hipGetErrorString(e));
     }
   }
@@ -1531,7 +1533,7 @@ vcr_status graph_run(vcr_ctx *c, const float *x0, int32_t B, float eps, const fl
         if (c->root_cache) HIP_TRY(c, hipFree(c->root_cache));
         c->root_cache = nullptr;
         c->root_cache_cap = 0;
-        HIP_TRY(c, hipMalloc(&c->root_cache, sizeof(float) * cache_floats));
+        HIP_TRY(c, device_alloc(c, reinterpret_cast<void **>(&c->root_cache), sizeof(float) * cache_floats));
         c->root_cache_cap = cache_floats;
       }
       st = cache_copy(true);

@@ -1,0 +1,75 @@
+"""Split weights and device memory: an allocation of the context that fits only in their place takes
+it, one that does not fit even there leaves them, a later call makes them again when there is
+room; the bounds are the same bits throughout, replayed graphs included."""
+import contextlib
+
+import numpy as np
+import pytest
+
+from paper_2606_09377_amd.vcrown import OPT_GRAPH, VCR_ERR_OOM, VcrError
+from tests.gpu_util import gpu_ctx, to_dev
+from workloads import random_mlp
+
+pytestmark = pytest.mark.gpu
+
+DIMS = [1024] + 5 * [4096] + [3]   # 0.86 GB of split weights; a workspace of 0.3 GB an input
+FREE = 3 << 30                     # left free beside the copies and the first workspace
+
+
+@contextlib.contextmanager
+def free_memory(left):
+    import torch
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    hold = torch.empty(max(torch.cuda.mem_get_info()[0] - left, 1), dtype=torch.uint8, device="cuda")
+    try:
+        yield
+    finally:
+        del hold
+        torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("replay", [False, True])
+def test_room_taken_and_regained(replay):
+    import torch
+    wl = random_mlp(991, DIMS, 1, 0.002)
+    ctx = gpu_ctx(wl.net)
+    if replay:
+        ctx.set_option(OPT_GRAPH, 1)
+    x0, C = to_dev(wl.x0), to_dev(wl.C)
+    with_copies = ctx.stats()["net_bytes"]
+
+    def one():
+        got = []
+        for _ in range(3):   # with replay: launched and recorded, then replayed twice
+            lb, ub = ctx.crown_bounds(x0, wl.eps, C)
+            torch.cuda.synchronize()
+            got += [lb.cpu().numpy(), ub.cpu().numpy()]
+        assert all(np.array_equal(g, got[k % 2]) for k, g in enumerate(got))
+        return got[:2]
+
+    want = one()
+    copies = 12 * (1024 * 4096 + 4 * 4096 * 4096)
+    xb, cb = x0.repeat(64, 1), C.repeat(64, 1, 1)
+    assert ctx.workspace_bytes(64, 2) > 5 * FREE and ctx.workspace_bytes(8, 2) < FREE
+    with free_memory(FREE):
+        # not even in their place: the call fails, the copies stay
+        with pytest.raises(VcrError) as e:
+            ctx.crown_bounds(xb, wl.eps, cb)
+        assert e.value.status == VCR_ERR_OOM
+        assert ctx.stats()["net_bytes"] == with_copies
+        assert all(np.array_equal(a, b) for a, b in zip(one(), want))
+        # workspaces grown by less than the copies hold: one of them takes their place
+        B = 8
+        while ctx.stats()["net_bytes"] == with_copies:
+            B += 1
+            lb, ub = ctx.crown_bounds(xb[:B], wl.eps, cb[:B])
+            torch.cuda.synchronize()
+            for b in (0, B - 1):
+                assert np.array_equal(lb[b].cpu().numpy(), want[0][0]) and np.array_equal(ub[b].cpu().numpy(), want[1][0])
+        assert ctx.stats()["net_bytes"] == with_copies - copies
+        assert all(np.array_equal(a, b) for a, b in zip(one(), want))
+        assert ctx.stats()["net_bytes"] == with_copies - copies
+    # room again
+    assert all(np.array_equal(a, b) for a, b in zip(one(), want))
+    assert ctx.stats()["net_bytes"] == with_copies
