@@ -25,7 +25,6 @@
 #include <cstdio>
 #include <cstring>
 #include <deque>
-#include <memory>
 #include <string>
 #include <vector>
 
@@ -521,9 +520,9 @@ vcr_status vcr_load_net(vcr_ctx *c, const vcr_node *nodes, int32_t n, const int3
   c->loaded = false;
   c->relu_n.clear();
   c->n0 = in_chw[0];
-  // one allocation for every layer's arrays and one staging buffer of the largest layer
+  // one allocation for every layer's arrays
   int64_t prev = in_chw[0];
-  size_t bytes = 0, staging_bytes = 0;
+  size_t bytes = 0;
   for (int32_t i = 0; i < n; ++i) {
     if (nodes[i].op == VCR_RELU) {
       c->relu_n.push_back((int32_t)prev);
@@ -536,17 +535,13 @@ vcr_status vcr_load_net(vcr_ctx *c, const vcr_node *nodes, int32_t n, const int3
     L.ld_out = ld_of(L.n_out);
     c->layers.push_back(L);
     bytes += 2 * al(sizeof(float) * (size_t)L.ld_out * L.ld_in) + al(sizeof(float) * (size_t)L.ld_out);
-    staging_bytes = std::max(staging_bytes, sizeof(float) * (size_t)L.n_out * L.n_in);
     prev = L.n_out;
   }
   HIP_TRY(c, hipMalloc(&c->layer_base, bytes));
-  float *staging = nullptr;
-  HIP_TRY(c, hipMalloc(&staging, staging_bytes));
-  struct Free {
-    float *p;
-    ~Free() { (void)hipFree(p); }
-  };
-  std::unique_ptr<Free> staging_owner(new Free{staging});
+  struct Wait {   // the caller's arrays are read until the copies have run, also when one fails
+    hipStream_t s;
+    ~Wait() { (void)hipStreamSynchronize(s); }
+  } wait{c->stream};
   Workspace w;
   w.base = static_cast<char *>(c->layer_base);
   w.cap = bytes;
@@ -557,16 +552,16 @@ vcr_status vcr_load_net(vcr_ctx *c, const vcr_node *nodes, int32_t n, const int3
     L.Wp = take<float>(w, (size_t)L.ld_out * L.ld_in);
     L.Bt = take<float>(w, (size_t)L.ld_in * L.ld_out);
     L.b = take<float>(w, (size_t)L.ld_out);
-    HIP_TRY(c, hipMemcpyAsync(staging, nodes[i].W, sizeof(float) * (size_t)L.n_out * L.n_in, hipMemcpyHostToDevice,
+    // the weights as given go through Wp's memory: the largest network that fits needs no more
+    HIP_TRY(c, hipMemcpyAsync(L.Wp, nodes[i].W, sizeof(float) * (size_t)L.n_out * L.n_in, hipMemcpyHostToDevice,
                               c->stream));
     // Wp: row-major copy, zero-padded to [ld_out][ld_in] (a transpose of the transpose); the
     // alpha-CROWN gradient pass uses it as a GEMM operand
-    HIP_TRY(c, launch_transpose_pad(staging, L.n_out, L.n_in, L.Bt, L.ld_out, L.ld_in, c->stream));
+    HIP_TRY(c, launch_transpose_pad(L.Wp, L.n_out, L.n_in, L.Bt, L.ld_out, L.ld_in, c->stream));
     HIP_TRY(c, launch_transpose_pad(L.Bt, (int32_t)L.ld_in, (int32_t)L.ld_out, L.Wp, L.ld_in, L.ld_out, c->stream));
     HIP_TRY(c, launch_fill(L.b, L.ld_out, 0.f, c->stream));
     HIP_TRY(c, hipMemcpyAsync(L.b, nodes[i].b, sizeof(float) * L.n_out, hipMemcpyHostToDevice, c->stream));
   }
-  staging_owner.reset();   // waits for the copies
   c->net_bytes = 0;
   for (const DenseLayer &L : c->layers)
     c->net_bytes += sizeof(float) * (2 * (uint64_t)L.ld_in * L.ld_out + (uint64_t)L.ld_out);

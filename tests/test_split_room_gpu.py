@@ -7,8 +7,8 @@ import numpy as np
 import pytest
 
 from paper_2606_09377_amd.vcrown import OPT_GRAPH, VCR_ERR_OOM, VcrError
-from tests.gpu_util import gpu_ctx, to_dev
-from workloads import random_mlp
+from tests.gpu_util import assert_close, gpu_ctx, to_dev
+from workloads import Net, Node, random_mlp
 
 pytestmark = pytest.mark.gpu
 
@@ -73,3 +73,23 @@ def test_room_taken_and_regained(replay):
     # room again
     assert all(np.array_equal(a, b) for a, b in zip(one(), want))
     assert ctx.stats()["net_bytes"] == with_copies
+
+
+def test_load_needs_the_layers_room_only():
+    """2.1 GB of layer arrays load into 2.5 GB: no copy of the largest layer (1 GB) beside them."""
+    import torch
+    n = 16384
+    rng = np.random.default_rng(5)
+    W = np.zeros((n, n), np.float32)
+    W[np.arange(n), rng.permutation(n)] = 1
+    net = Net((n,), [Node("dense", -1, W=W, b=np.zeros(n, np.float32)), Node("relu", 0),
+                     Node("dense", 1, W=rng.standard_normal((4, n)).astype(np.float32), b=np.ones(4, np.float32))])
+    x0 = rng.random((1, n)).astype(np.float32)
+    with free_memory(2500 << 20):
+        ctx = gpu_ctx(net)
+        assert 2 * 4 * n * n <= ctx.stats()["net_bytes"] < 2 * 4 * n * n + (32 << 20)
+    lb, ub = ctx.crown_bounds(to_dev(x0), np.float32(0), to_dev(np.eye(4, dtype=np.float32)[None]))
+    torch.cuda.synchronize()
+    want = net.nodes[2].W.astype(np.float64) @ (W @ x0[0]) + 1
+    assert_close(lb[0].cpu().numpy(), want, "lb")
+    assert_close(ub[0].cpu().numpy(), want, "ub")
