@@ -145,7 +145,8 @@ enum {
  * operand layout, vcr_stats.net_bytes), about 1.2 times slower, 1.5 on single inputs: what SPLIT
  * does by itself while the copies would leave less than an eighth of the device's memory free, and
  * once an allocation of the context has taken their place (a later call makes them again when
- * there is room). */
+ * there is room).  Copies that a call under the caller's own stream capture has used stay until
+ * the next vcr_load_net, since the recorded graph reads them. */
 enum {
   VCR_PRODUCTS_SPLIT = 0,
   VCR_PRODUCTS_FLOAT32 = 1,

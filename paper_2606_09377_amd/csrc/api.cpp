@@ -194,14 +194,21 @@ void drop_split_copies(vcr_ctx *c) {
 void forget_split_operands(vcr_ctx *c) {
   drop_split_copies(c);
   c->split_items.clear();
+  c->split_held = false;
+}
+
+bool hold_split_copies_in_capture(vcr_ctx *c) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) (void)hipGetLastError();
+  if (cap == hipStreamCaptureStatusNone) return false;
+  if (c->split_base) c->split_held = true;
+  return true;
 }
 
 vcr_status regain_split_copies(vcr_ctx *c) {
-  if (c->split_base || c->split_items.empty() || c->net_products != VCR_PRODUCTS_SPLIT) return VCR_OK;
+  if (c->split_items.empty() || c->net_products != VCR_PRODUCTS_SPLIT) return VCR_OK;
   HIP_TRY(c, hipSetDevice(c->device));
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(c->stream, &cap) != hipSuccess) (void)hipGetLastError();
-  return cap == hipStreamCaptureStatusNone ? make_split_copies(c) : VCR_OK;   // no allocation in a capture
+  return hold_split_copies_in_capture(c) ? VCR_OK : make_split_copies(c);   // no allocation in a capture
 }
 
 hipError_t device_alloc(vcr_ctx *c, void **p, size_t bytes) {
@@ -210,7 +217,7 @@ hipError_t device_alloc(vcr_ctx *c, void **p, size_t bytes) {
   (void)hipGetLastError();
   size_t free_b = 0, total_b = 0;
   // (the driver gives somewhat more than it reports as free)
-  if (!c->split_base || hipMemGetInfo(&free_b, &total_b) != hipSuccess ||
+  if (!c->split_base || c->split_held || hipMemGetInfo(&free_b, &total_b) != hipSuccess ||
       free_b + total_b / 64 + c->split_bytes < bytes)
     return e;
   drop_split_copies(c);
@@ -1321,6 +1328,7 @@ vcr_status vcr::crown_bounds_in(vcr_ctx *c, const float *x0, int32_t B, float ep
   if (st != VCR_OK)
     return fail(c, VCR_ERR_OOM, "the call does not fit the %llu-byte scratch even one input at a time (%s)",
                 (unsigned long long)cap, c->err.c_str());
+  (void)hold_split_copies_in_capture(c);
   const Workspace own = c->ws;
   const int32_t timing = c->time_gemm;
   c->ws = Workspace{base, cap, 0};

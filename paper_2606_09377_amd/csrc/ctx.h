@@ -79,6 +79,7 @@ struct vcr_ctx {
   std::vector<SplitItem> split_items;
   void *split_base = nullptr;
   uint64_t split_bytes = 0;
+  bool split_held = false;  // a graph that the caller recorded reads them: they stay until the next load
   int32_t net_products = 0; // VCR_PRODUCTS_* of the loaded network
   uint64_t net_bytes = 0;   // device memory holding the loaded network (weights in their layouts)
   // last call
@@ -197,6 +198,8 @@ vcr_status make_split_copies(vcr_ctx *c);
 void drop_split_copies(vcr_ctx *c);
 // Forgets the network's operands too (before its weights are freed or replaced).
 void forget_split_operands(vcr_ctx *c);
+// Whether the caller records the context's stream: the copies are then kept for the recorded graph.
+bool hold_split_copies_in_capture(vcr_ctx *c);
 // Start of a call that may allocate: makes missing copies if there is room now.
 vcr_status regain_split_copies(vcr_ctx *c);
 // hipMalloc, in the place of the split copies if it fails beside them.

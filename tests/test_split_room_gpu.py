@@ -75,6 +75,45 @@ def test_room_taken_and_regained(replay):
     assert ctx.stats()["net_bytes"] == with_copies
 
 
+def test_a_recorded_graph_keeps_the_copies():
+    """A caller's graph of an allocation-free call reads the copies: a workspace that fits only in
+    their place fails, and the graph replays the same bits, with eager calls between."""
+    import torch
+    wl = random_mlp(992, [16384, 2048, 2048, 3], 1, 0.002)   # 0.45 GB of split weights
+    ctx = gpu_ctx(wl.net)
+    x0, C = to_dev(wl.x0), to_dev(wl.C)
+    m = C.shape[1]
+    lb, ub = torch.empty(1, m, device="cuda"), torch.empty(1, m, device="cuda")
+    ctx.crown_bounds_noalloc(x0, wl.eps, C, (lb, ub))
+    want = [lb.cpu().numpy(), ub.cpu().numpy()]
+    with_copies = ctx.stats()["net_bytes"]
+    copies = 12 * (16384 * 2048 + 2048 * 2048)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        ctx.crown_bounds_noalloc(x0, wl.eps, C, (lb, ub))
+
+    def replay():
+        lb.zero_()
+        ub.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(lb.cpu().numpy(), want[0]) and np.array_equal(ub.cpu().numpy(), want[1])
+
+    replay()
+    xb, cb = x0.repeat(200, 1), C.repeat(200, 1, 1)
+    with free_memory(1 << 30):
+        with pytest.raises(VcrError) as e:
+            for B in range(2, 201):   # workspaces grown by less than the copies hold
+                assert ctx.workspace_bytes(B, m) - ctx.workspace_bytes(B - 1, m) < copies
+                ctx.crown_bounds(xb[:B], wl.eps, cb[:B])
+                torch.cuda.synchronize()
+                replay()
+        assert e.value.status == VCR_ERR_OOM
+        assert ctx.stats()["net_bytes"] == with_copies
+        replay()
+    replay()
+
+
 def test_load_needs_the_layers_room_only():
     """2.1 GB of layer arrays load into 2.5 GB: no copy of the largest layer (1 GB) beside them."""
     import torch
