@@ -169,6 +169,9 @@ vcr_status make_split_copies(vcr_ctx *c, size_t spare) {
     }
     off += split_size(it);
   }
+  // the next call may come on another stream, and after a call that failed there is nothing the
+  // caller would wait for
+  HIP_TRY(c, hipStreamSynchronize(c->stream));
   return VCR_OK;
 }
 }  // namespace

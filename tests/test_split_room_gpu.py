@@ -114,6 +114,33 @@ def test_a_recorded_graph_keeps_the_copies():
     replay()
 
 
+def test_copies_made_again_are_whole_for_the_next_stream():
+    """A request that fails in the copies' place too has them made again; the next call, on another
+    stream and with nothing waited for, finds them whole."""
+    import torch
+    wl = random_mlp(993, DIMS, 1, 0.002)
+    ctx = gpu_ctx(wl.net)
+    x0, C = to_dev(wl.x0), to_dev(wl.C)
+    want = [t.cpu().numpy() for t in ctx.crown_bounds(x0, wl.eps, C)]
+    with_copies = ctx.stats()["net_bytes"]
+    m, free = C.shape[1], 1 << 30
+    side = torch.cuda.Stream()
+    with free_memory(free):
+        B = 2   # about 3 GB more than is free
+        while ctx.workspace_bytes(B, m) < free + (3 << 30):
+            B += 1
+        xb, cb = x0.expand(B, -1).contiguous(), C.expand(B, -1, -1).contiguous()
+        torch.cuda.synchronize()
+        with pytest.raises(VcrError) as e:
+            ctx.crown_bounds(xb, wl.eps, cb)
+        assert e.value.status == VCR_ERR_OOM
+        with torch.cuda.stream(side):
+            lb, ub = ctx.crown_bounds(x0, wl.eps, C)
+        side.synchronize()
+        assert np.array_equal(lb.cpu().numpy(), want[0]) and np.array_equal(ub.cpu().numpy(), want[1])
+    assert ctx.stats()["net_bytes"] == with_copies
+
+
 def test_load_needs_the_layers_room_only():
     """2.1 GB of layer arrays load into 2.5 GB: no copy of the largest layer (1 GB) beside them."""
     import torch
