@@ -410,14 +410,17 @@ static bool use_split(const GemmArgs &a) { return !a.float32 && std::max(a.lda, 
 
 // 0: SplitL, 3: SplitM, 2: SplitS.  In its own loop (K = 1024, N = 1024) SplitL reaches 228
 // TFLOP/s and SplitM 187; SplitL holds 512 workgroups on the chip at once, so it runs where its
-// rounds of 512 are full enough to keep that lead.  SplitM overtakes SplitS between 256 tiles
-// (64 x 64; 158 us against 131 at K = 8192) and 512 (29 us against 32 at K = 1024).
+// rounds of 512 are full enough to keep that lead.  SplitS runs up to 256 tiles of 64 x 64, two
+// of its own per compute unit; beyond, its third one costs more than SplitM's larger tile (us, SplitS
+// against SplitM, at 256 and at 320 tiles: K = 512 12.7 / 12.5 and 16.0 / 14.4, K = 1024 20.6 / 21.5
+// and 26.9 / 23.8, K = 8192 133 / 141 and 179 / 154, K = 32768 552 / 714 and 683 / 717; at 384 SplitM
+// leads by 5 to 27%).
 static int split_kind(const GemmArgs &a) {
   const int64_t big = (int64_t)((a.M + 127) / 128) * (a.N_pad / 128);
   const int64_t rounds = (big + 511) / 512;
   if (big >= 512 && big * 100 >= rounds * 512 * 82) return 0;
   const int64_t mid = (int64_t)((a.M + 63) / 64) * (a.N_pad / 64);
-  return mid > 384 ? 3 : 2;
+  return mid > 256 ? 3 : 2;
 }
 
 }  // namespace vcr
