@@ -40,16 +40,16 @@ def test_constants_over_changing_widths(dims):
 
 
 def test_every_tile_shape_gives_the_same_bits():
-    """640 rows an input: one input runs the 32 x 64 and 64 x 64 tiles, 64 inputs (40960 rows)
-    the 128 x 128 ones; the inputs are the same."""
+    """640 rows an input and six columns of 64: one input runs the 32 x 64 tiles, 8 inputs (480 tiles of
+    64 x 64) the 64 x 64 ones and 64 inputs (960 of 128 x 128) the 128 x 128 ones."""
     wl = random_mlp(931, [300, 320, 320, 320, 11], 64, 0.01)
     ctx = gpu_ctx(wl.net)
     lb, ub, layers = gpu_crown(ctx, wl)
-    for b in (0, 37, 63):
-        l1, u1, lay1 = gpu_crown(ctx, wl, inputs=[b])
-        assert np.array_equal(l1[0], lb[b]) and np.array_equal(u1[0], ub[b])
-        for (l, u), (lx, ux) in zip(layers, lay1):
-            assert np.array_equal(lx[0], l[b]) and np.array_equal(ux[0], u[b])
+    for sel in ([0], [37], [63], [5, 9, 11, 20, 37, 41, 62, 63]):
+        ls, us, lays = gpu_crown(ctx, wl, inputs=sel)
+        assert np.array_equal(ls, lb[sel]) and np.array_equal(us, ub[sel])
+        for (l, u), (lx, ux) in zip(layers, lays):
+            assert np.array_equal(lx, l[sel]) and np.array_equal(ux, u[sel])
     check_input(wl.net, wl.x0[37], wl.eps, wl.C[37], lb[37], ub[37], [(l[37], u[37]) for l, u in layers])
 
 

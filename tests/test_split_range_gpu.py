@@ -66,9 +66,9 @@ def test_every_tile_shape_out_of_range():
     blb, bub, _ = gpu_crown(ctx, base)
     for g, w in ((blb, lb), (bub, ub)):
         assert_close(g.astype(np.float64) * 2.0 ** -110, w.astype(np.float64), "scaled bounds")
-    for b in (0, 63):
-        l1, u1, _ = gpu_crown(ctx, base, inputs=[b])
-        assert np.array_equal(l1[0], blb[b]) and np.array_equal(u1[0], bub[b])
+    for sel in ([0], [63], [5, 9, 11, 20, 37, 41, 62, 63]):   # the 32 x 64 and the 64 x 64 tiles
+        ls, us, _ = gpu_crown(ctx, base, inputs=sel)
+        assert np.array_equal(ls, blb[sel]) and np.array_equal(us, bub[sel])
 
 
 def test_the_largest_finite_weight_times_zero():
