@@ -57,18 +57,17 @@ constexpr int GEMM_MINB = BK == 32 ? 2 : 3;   // workgroups per CU the registers
 constexpr int NTHREADS = 256;
 constexpr int GROUP_M = 8;
 
-__device__ __forceinline__ void map_tile(int bid, int G, int n_mt, int n_nt, int &mt, int &nt,
-                                         int group_m = GROUP_M) {
+__device__ __forceinline__ void map_tile(int bid, int G, int n_mt, int n_nt, int &mt, int &nt) {
   // Workgroup ids are spread over the 8 XCDs round robin; hand each XCD a contiguous range
   // of logical tiles so the tiles sharing operands also share that XCD's L2.
   const int x = bid & 7, t = bid >> 3;
   const int q = G >> 3, rem = G & 7;
   const int logical = x * q + min(x, rem) + t;
-  // Grouped order: group_m row blocks sweep every column tile together.
-  const int per_group = group_m * n_nt;
+  // Grouped order: GROUP_M row blocks sweep every column tile together.
+  const int per_group = GROUP_M * n_nt;
   const int g = logical / per_group;
-  const int first_m = g * group_m;
-  const int gm = min(group_m, n_mt - first_m);
+  const int first_m = g * GROUP_M;
+  const int gm = min(GROUP_M, n_mt - first_m);
   const int idx = logical - g * per_group;
   mt = first_m + idx % gm;
   nt = idx / gm;

@@ -242,13 +242,13 @@ __global__ __launch_bounds__(TS::T, TS::MINB) void k_gemm_split(const GemmArgs p
   // chunk; the chunk that lands in a slot is swizzled by lds_swz, the swizzle applied on the
   // fetch side), or as many rows of float32 weights, or one part of a 16-column block of weights.
   constexpr int AI = TS::BM / 8, BI = WF ? TS::BN / 8 : 3 * (TS::BN / 16);
-  constexpr int AQ = (AI + NW - 1) / NW, BQ = (BI + NW - 1) / NW;
-  static_assert(AI % NW == 0 || AI < NW, "loads spread evenly over the waves");
+  constexpr int AQ = AI / NW, BQ = BI / NW;
+  static_assert(AI % NW == 0 && BI % NW == 0, "loads spread evenly over the waves");
   const int kblocks = p.K / 32;
   uint32_t a_off[AQ];   // bytes from the tile's first row, under 2^32 (use_split)
 #pragma unroll
   for (int q = 0; q < AQ; ++q) {
-    const int row = (AI < NW ? wave % AI : q * NW + wave) * 8 + (lane >> 3);
+    const int row = (q * NW + wave) * 8 + (lane >> 3);
     a_off[q] = (uint32_t)row * (uint32_t)(p.lda * 4) + ((lane & 7) ^ lds_swz<32>(row)) * 16;
   }
   const float *a_tile = p.A + (int64_t)m0 * p.lda;
@@ -256,13 +256,10 @@ __global__ __launch_bounds__(TS::T, TS::MINB) void k_gemm_split(const GemmArgs p
   const uint16_t *b_tile = WF ? nullptr : p.Bs + (int64_t)(n0 / 16) * kblocks * SPLIT_BLOCK;
   auto issue = [&](int kt, int buf) {
 #pragma unroll
-    for (int q = 0; q < AQ; ++q) {
-      const int i = AI < NW ? wave % AI : q * NW + wave;   // fewer loads than waves: some repeat one
-      dma16(a_tile + kt * 32, a_off[q], As + buf * TS::A_FLOATS + i * 256);
-    }
+    for (int q = 0; q < AQ; ++q) dma16(a_tile + kt * 32, a_off[q], As + buf * TS::A_FLOATS + (q * NW + wave) * 256);
 #pragma unroll
     for (int q = 0; q < BQ; ++q) {
-      const int i = min(q * NW + wave, BI - 1);
+      const int i = q * NW + wave;
       if constexpr (WF) {
         const int row = i * 8 + (lane >> 3);
         dma16(w_tile + kt * 32, (uint32_t)row * (uint32_t)(p.ldb * 4) + ((lane & 7) ^ lds_swz<32>(row)) * 16,
@@ -274,7 +271,7 @@ __global__ __launch_bounds__(TS::T, TS::MINB) void k_gemm_split(const GemmArgs p
       }
     }
   };
-  constexpr int LPT = AQ + BQ;   // loads of a wave per K step
+  [[maybe_unused]] constexpr int LPT = AQ + BQ;   // loads of a wave per K step
 
   f32v4 hi[MB][NB], lo[MB][NB];
 #pragma unroll
@@ -299,17 +296,14 @@ __global__ __launch_bounds__(TS::T, TS::MINB) void k_gemm_split(const GemmArgs p
     auto read = [&](int buf, SplitRaw<MB, NB> &r) {
       split_read<MB, NB, AFF, WF>(r, as + buf * TS::A_FLOATS, ch0, ch1, b_lane + buf * TS::B_FLOATS, abs_mask);
     };
-    auto landed = [&](int later) {   // with `later` steps requested after the one waited for
-      if (NS >= 4 && later >= 2) wait_vmcnt<(NS >= 4 ? 2 : 0) * LPT>();
-      else if (NS >= 3 && later >= 1) wait_vmcnt<(NS >= 3 ? 1 : 0) * LPT>();
-      else wait_vmcnt<0>();
-      barrier_only();
-    };
+    static_assert(NS == 3, "one step in flight behind the one waited for");
     int cur = 0;   // step kt's stage
     auto step = [&](int kt, const SplitRaw<MB, NB> &now, SplitRaw<MB, NB> &next) {
       const int nxt = cur + 1 == NS ? 0 : cur + 1;
       if (kt + 1 < KT) {
-        landed(min(NS - 2, KT - 2 - kt));
+        if (kt + 2 < KT) wait_vmcnt<LPT>();
+        else wait_vmcnt<0>();
+        barrier_only();
         if (kt + NS < KT) issue(kt + NS, cur);
         read(nxt, next);
       }
@@ -328,17 +322,15 @@ __global__ __launch_bounds__(TS::T, TS::MINB) void k_gemm_split(const GemmArgs p
       if (kt + 1 < KT) step(kt + 1, r1, r0);
     }
   } else {
+    static_assert(NS == 2, "no step in flight behind the one waited for");
     int cur = 0;
     for (int kt = 0; kt < KT; ++kt) {
-      // this wave's part of step kt has landed (the next NS - 2 steps may be in flight)
-      if (NS >= 3 && kt + 1 < KT) wait_vmcnt<NS >= 3 ? LPT : 0>();
-      else wait_vmcnt<0>();
-      static_assert(TS::PIPE || NS <= 3, "the waits assume at most one later step in flight");
-      barrier_only();   // every wave's part of step kt is in LDS, and step kt - 1's stage is free
-      if (kt + NS - 1 < KT) issue(kt + NS - 1, cur + NS - 1 >= NS ? cur - 1 : cur + NS - 1);
+      wait_vmcnt<0>();   // this wave's part of step kt has landed
+      barrier_only();    // every wave's has, and step kt - 1's stage is free
+      if (kt + 1 < KT) issue(kt + 1, cur ^ 1);
       const float *as = As + cur * TS::A_FLOATS + (wm * (TS::BM / TS::WM) + r16) * 32;
       split_step<MB, NB, AFF, WF>(as, ch0, ch1, b_lane + cur * TS::B_FLOATS, nj, abs_mask, hi, lo);
-      cur = cur + 1 == NS ? 0 : cur + 1;
+      cur ^= 1;
     }
   }
   {

@@ -84,7 +84,8 @@ struct GemmArgs {
 };
 
 hipError_t launch_gemm(const GemmArgs &a, hipStream_t s);
-// The kernel launch_gemm runs for these arguments: 0 k_gemm, 2 k_gemm_small, 3 k_gemm_mid.
+// The tiles launch_gemm runs for these arguments: 0 of 128 x 128 (k_gemm_split's SplitL; k_gemm), 2 of 32 x 64
+// (SplitS; k_gemm_small), 3 of 64 x 64 (SplitM; k_gemm_mid).
 int gemm_kind(const GemmArgs &a);
 
 // Split copy (split_bf16.h) of weights src [N][K] of pitch ld: N a multiple of 16, K of 32;
