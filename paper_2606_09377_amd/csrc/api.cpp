@@ -143,13 +143,13 @@ vcr_status ensure_ws(vcr_ctx *c, size_t bytes) {
 namespace {
 size_t split_size(const SplitItem &it) { return al(sizeof(uint16_t) * 3 * (size_t)it.N * (size_t)it.K); }
 
-// the copies, if device memory is there for them and `spare` more bytes
-vcr_status make_split_copies(vcr_ctx *c, size_t spare) {
+// the copies, if device memory is there for them and (spare) an eighth of all of it beside them
+vcr_status make_split_copies(vcr_ctx *c, bool spare) {
   size_t bytes = 0, free_b = 0, total_b = 0;
   for (const SplitItem &it : c->split_items) bytes += split_size(it);
   if (bytes == 0 || c->split_base || c->net_products != VCR_PRODUCTS_SPLIT) return VCR_OK;
   HIP_TRY(c, hipMemGetInfo(&free_b, &total_b));
-  if (bytes + spare > free_b) return VCR_OK;
+  if (bytes + (spare ? total_b / 8 : 0) > free_b) return VCR_OK;
   void *base = nullptr;
   if (hipMalloc(&base, bytes) != hipSuccess) {
     (void)hipGetLastError();
@@ -176,12 +176,7 @@ vcr_status make_split_copies(vcr_ctx *c, size_t spare) {
 }
 }  // namespace
 
-vcr_status make_split_copies(vcr_ctx *c) {
-  size_t free_b = 0, total_b = 0;
-  if (c->split_items.empty() || c->split_base || c->net_products != VCR_PRODUCTS_SPLIT) return VCR_OK;
-  HIP_TRY(c, hipMemGetInfo(&free_b, &total_b));
-  return make_split_copies(c, total_b / 8);
-}
+vcr_status make_split_copies(vcr_ctx *c) { return make_split_copies(c, true); }
 
 void drop_split_copies(vcr_ctx *c) {
   for (const SplitItem &it : c->split_items) *it.dst = nullptr;
@@ -227,7 +222,7 @@ hipError_t device_alloc(vcr_ctx *c, void **p, size_t bytes) {
   e = hipMalloc(p, bytes);
   if (e == hipSuccess) return e;
   (void)hipGetLastError();
-  (void)make_split_copies(c, 0);   // that did not help: as they were
+  (void)make_split_copies(c, false);   // that did not help: as they were
   return e;
 }
 
