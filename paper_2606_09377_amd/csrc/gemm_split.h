@@ -313,7 +313,9 @@ __global__ __launch_bounds__(TS::T, TS::MINB) void k_gemm_split(const GemmArgs p
     SplitRaw<MB, NB> r0, r1;
     if (KT > 0) {
       if (NS - 1 < KT) issue(NS - 1, NS - 1);
-      wait_vmcnt<0>();
+      if (KT >= NS) wait_vmcnt<2 * LPT>();   // the first step has landed, the other stages' are in flight
+      else if (KT == 2) wait_vmcnt<LPT>();
+      else wait_vmcnt<0>();
       barrier_only();
       read(0, r0);
     }
