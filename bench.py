@@ -7,7 +7,7 @@ the ReLU relaxations and the final spec pass.  Default workload: the wide ReLU M
 99 margin rows per input, with its 8192 x 8192 A matrices held whole (146.6 TFLOP per call).
 
 Prints one JSON line with the throughput (inputs/s), the dominant kernel's roofline
-(the backward-step fp32 MFMA GEMM, timed with HIP events on the stream it runs on) and the
+(the backward-step GEMM, timed with HIP events on the stream it runs on) and the
 fp64 CPU oracle timed on a bounded sample of the same workload.
 """
 from __future__ import annotations

@@ -241,6 +241,8 @@ __global__ __launch_bounds__(TS::T, TS::MINB) void k_gemm_split(const GemmArgs p
   // One load of a wave fills 1 KB of LDS in lane order: 8 coefficient rows (lane = row, 16-byte
   // chunk; the chunk that lands in a slot is swizzled by lds_swz, the swizzle applied on the
   // fetch side), or as many rows of float32 weights, or one part of a 16-column block of weights.
+  // (By the counters each 16-byte read of coefficients still spends 4 cycles on bank conflicts, a
+  // read of split weights none.)
   constexpr int AI = TS::BM / 8, BI = WF ? TS::BN / 8 : 3 * (TS::BN / 16);
   constexpr int AQ = AI / NW, BQ = BI / NW;
   static_assert(AI % NW == 0 && BI % NW == 0, "loads spread evenly over the waves");

@@ -30,8 +30,8 @@
 // 1024: 1.9e-7 of the result against 5.7e-7; K = 65536: 1.6e-6 against 4.6e-6).
 //
 // Why: the float32 matrix rate of gfx950 is 157 TFLOP/s; six bf16 products run at a sixth of
-// 2.5 PFLOP/s nominal, 305 TFLOP/s of float32 products measured with every operand in
-// registers (the card's power limit sets that rate, not the issue rate).
+// 2.5 PFLOP/s nominal, 338 to 352 TFLOP/s of float32 products measured with random operands in
+// registers, 406 to 414 with zeros (the card's power limit sets the rate, not the issue).
 //
 // Instruction: v_mfma_f32_16x16x32_bf16, in this order of partial products for every K step of
 // 32 everywhere, so that a result does not depend on which tile size computed it.  The 32x32x16
